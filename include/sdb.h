@@ -359,7 +359,13 @@ enum { SDB_LDS_GLOBAL = 0, SDB_LDS_MAP = 1, SDB_LDS_BITS = 2, SDB_LDS_RANK = 3, 
  * rows that can pass the join; the planner takes it when the join's sampled
  * pass fraction, with the filter's false positives added, is at most 0.7
  * (each dropped row saves a scatter write and a probe, each row costs one
- * L2-resident filter read). It needs
+ * L2-resident filter read). Where the passing rows of a 2,048th of the table
+ * or more fit an LDS table (up to about 8.9M passing rows), the run takes
+ * another route when its scratch holds it, as run_scratch_bytes always does:
+ * the rows are partitioned so finely (256 to 2,048 slices) that a block sums
+ * each slice's rows by dimension row in LDS and only those totals go to their
+ * groups; rows that cannot pass find no entry there, so it tests no pass
+ * filter. It needs
  * one hash probe, all other stages fact predicates, and the columns those
  * passes read 16-byte aligned. ipt, vector, eager (0), block, grid,
  * lds_bytes and the terminal fields describe that fused launch. */

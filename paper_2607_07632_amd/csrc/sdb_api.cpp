@@ -1036,6 +1036,60 @@ SliceLayout slice_layout(const sdb_query* q, const sdb_plan* plan) {
     return L;
 }
 
+// The LDS route of a sliced probe (slice_agg_kernel): as many partitions as
+// leave at most 8/9 of kSliceAggEntries passing keys to each (2^kSliceAggMinBits at
+// least, where the table has that many slots), or 0 where even the most
+// partitions would overfill the LDS table: then the fused kernel probes the
+// slices through L2.
+int slice_agg_bits(const sdb_dim* d) {
+    int bits = kSliceAggMinBits;
+    while (bits < kSliceMaxBits && ((uint64_t)d->n_pass >> bits) > kSliceAggEntries / 9 * 8) ++bits;
+    if (((uint64_t)d->n_pass >> bits) > kSliceAggEntries / 18 * 17) return 0;
+    return std::min(bits, (int)d->hash_bits);
+}
+
+struct SliceAggLayout {
+    uint64_t hist, part_count, part_start, chunk_start, emit_fill, rec, rec_b, emit, total;
+    uint32_t emit_ranges, emit_cap;
+    int bits;
+};
+
+SliceAggLayout slice_agg_layout(const sdb_query* q, const sdb_plan* plan) {
+    SliceAggLayout L;
+    std::memset(&L, 0, sizeof L);
+    if (plan->slice_bits <= 0) return L;
+    const sdb_dim* d = q->joins[plan->stage_index[plan->slice_stage]].dim;
+    L.bits = slice_agg_bits(d);
+    if (L.bits == 0) return L;
+    const uint64_t P = 1ull << L.bits, n = (uint64_t)std::max<int64_t>(q->n_fact, 1);
+    const uint64_t ranges = (plan->n_groups + (1ull << kSliceEmitShift) - 1) >> kSliceEmitShift;
+    if (plan->n_groups > kSliceAggMaxGroups && ranges <= kSliceEmitMaxRanges) {
+        // an entry per passing dimension row and work item of its slice, twice
+        // the even share for each range of groups (the rest goes in with atomics)
+        const uint64_t per = (n / P + kSliceAggItem - 1) / kSliceAggItem;
+        const uint64_t entries = std::min<uint64_t>(n, (uint64_t)d->n_pass * std::max<uint64_t>(per, 1));
+        const uint64_t cap = ranges == 1 ? entries : std::min<uint64_t>(entries, 2 * entries / ranges + 1024);
+        L.emit_ranges = (uint32_t)ranges;
+        L.emit_cap = (uint32_t)std::max<uint64_t>(std::min<uint64_t>(cap, 1u << 30), 1);
+    }
+    uint64_t off = 0;
+    auto take = [&](uint64_t bytes) {
+        const uint64_t at = off;
+        off += align_up(bytes, 256);
+        return at;
+    };
+    L.hist = take(P * (uint64_t)plan->slice_grid * 4);
+    L.part_count = take(P * 4);
+    L.part_start = take((P + 1) * 4);
+    L.chunk_start = take((P + 1) * 4);
+    L.emit_fill = take((uint64_t)L.emit_ranges * 4);
+    L.rec = take(n * 8);
+    L.rec_b = q->agg.kind != SDB_AGG_COL ? take(n * 4) : 0;
+    L.emit = take((uint64_t)L.emit_ranges * L.emit_cap * 16);
+    L.total = off;
+    return L;
+}
+
 // Run scratch of the LDS_RANK stages' tables and the LDS_COARSE stages'
 // coarse bitmaps, in stage order; the terminal's scratch follows it.
 uint64_t stage_scratch_bytes(const sdb_query* q, const sdb_plan* plan) {
@@ -1886,7 +1940,9 @@ SDB_API sdb_status sdb_plan_star_query(const sdb_query* q, void* scratch, int64_
             const double fp = d->filter_kind == SDB_FILTER_BLOOM ? bloom_false_positive(d->filter_bits, d->n_pass) : 0.0;
             plan->slice_prefilter = (q->force_prefilter == 1 || p + (1.0 - p) * fp <= kPrefilterMaxKept) ? 1 : 0;
         }
-        plan->run_scratch_bytes += (int64_t)slice_layout(q, plan).total;
+        const int64_t copies = xcd ? (int64_t)copy_bytes : 0;
+        plan->run_scratch_bytes = std::max(plan->run_scratch_bytes + (int64_t)slice_layout(q, plan).total,
+                                           (int64_t)slice_agg_layout(q, plan).total + copies);
     }
     return ok();
 }
@@ -1986,8 +2042,15 @@ SDB_API sdb_status sdb_run_star_query(const sdb_query* q, const sdb_plan* plan, 
     p.ring_off = (uint32_t)plan->lds_bytes;
 
     hipStream_t s = (hipStream_t)stream;
+    // a sliced probe takes its LDS route where the table's slices fit LDS and
+    // the scratch holds that route's rows (a plan's run_scratch_bytes always does)
+    const SliceAggLayout AL = slice_agg_layout(q, plan);
+    const uint64_t copy_bytes = plan->xcd_copies ? term_scratch : 0;
+    const bool slice_agg = sliced && AL.bits > 0 && (uint64_t)scratch_bytes >= AL.total + copy_bytes;
     uint8_t* slice_base = (uint8_t*)scratch + stage_bytes;
-    uint8_t* term_base = slice_base + SL.total;
+    uint8_t* term_base = slice_base + (slice_agg ? AL.total : SL.total);
+    SliceAggParams ap;
+    std::memset(&ap, 0, sizeof ap);
     SliceParams sp;
     std::memset(&sp, 0, sizeof sp);
     if (sliced) {
@@ -2010,6 +2073,33 @@ SDB_API sdb_status sdb_run_star_query(const sdb_query* q, const sdb_plan* plan, 
             sp.pred[sp.n_preds] = lower_pred(pr);
             ++sp.n_preds;
         }
+    }
+    if (slice_agg) {
+        // (whole groups of four rows; no other rounding, so that every block has its share)
+        sp.rows_per_block = (int64_t)align_up((uint64_t)((q->n_fact + plan->slice_grid - 1) / plan->slice_grid), 4);
+        sp.bits = AL.bits;
+        sp.hist = (uint32_t*)(slice_base + AL.hist);
+        sp.part_count = (uint32_t*)(slice_base + AL.part_count);
+        sp.part_start = (uint32_t*)(slice_base + AL.part_start);
+        sp.chunk_start = (uint32_t*)(slice_base + AL.chunk_start);
+        sp.out_rec = (unsigned long long*)(slice_base + AL.rec);
+        sp.out_val2 = sp.val2_col >= 0 ? (int32_t*)(slice_base + AL.rec_b) : nullptr;
+        sp.item_rows = kSliceAggItem;
+        ap.st = p.st[plan->slice_stage];
+        ap.bits = AL.bits;
+        ap.agg_kind = q->agg.kind;
+        ap.part_start = sp.part_start;
+        ap.chunk_start = sp.chunk_start;
+        ap.rec = sp.out_rec;
+        ap.rec_b = sp.out_val2;
+        ap.n_groups = (uint32_t)plan->n_groups;
+        ap.emit_ranges = AL.emit_ranges;
+        ap.emit_cap = AL.emit_cap;
+        ap.emit_fill = (uint32_t*)(slice_base + AL.emit_fill);
+        ap.emit = (v4u_t*)(slice_base + AL.emit);
+        ap.lds_groups = !plan->xcd_copies && plan->n_groups <= kSliceAggMaxGroups ? (uint32_t)plan->n_groups : 0u;
+    } else if (sliced) {
+        const int ss = plan->slice_stage;
         sp.hist = (uint32_t*)(slice_base + SL.hist);
         sp.part_count = (uint32_t*)(slice_base + SL.part_count);
         sp.part_start = (uint32_t*)(slice_base + SL.part_start);
@@ -2100,7 +2190,7 @@ SDB_API sdb_status sdb_run_star_query(const sdb_query* q, const sdb_plan* plan, 
     p.xtab = plan->xcd_copies ? (unsigned long long*)term_base : nullptr;
     PartParams pp;
     std::memset(&pp, 0, sizeof pp);
-    if (plan->terminal == TERM_PART) {
+    if (plan->terminal == TERM_PART && !slice_agg) {
         const PartLayout L = part_layout(q, plan);
         uint8_t* base = term_base;
         p.region_count = (uint32_t*)(base + L.region_count);
@@ -2112,6 +2202,7 @@ SDB_API sdb_status sdb_run_star_query(const sdb_query* q, const sdb_plan* plan, 
         p.part_shift = plan->part_shift;
         p.n_parts = (uint32_t)plan->n_parts;
         p.part_subs = (uint32_t)plan->part_subs;
+        pp.chunk_rows = (uint32_t)kPartChunk;
         pp.n_groups = plan->n_groups;
         pp.part_shift = plan->part_shift;
         pp.n_parts = (uint32_t)plan->n_parts;
@@ -2132,7 +2223,21 @@ SDB_API sdb_status sdb_run_star_query(const sdb_query* q, const sdb_plan* plan, 
         pp.sums = p.sums;
         pp.counts = p.counts;
     }
-    if (q->n_fact > 0) {
+    if (q->n_fact > 0 && slice_agg) {
+        DeviceInfo di;
+        st = device_info(&di);
+        if (st != SDB_OK) return st;
+        ap.sums = p.sums;
+        ap.counts = p.counts;
+        ap.xcd_copies = p.xcd_copies;
+        ap.xtab = p.xtab;
+        const bool timed = g_fused_start && g_fused_stop;
+        if (timed) SDB_HIP(hipEventRecord(g_fused_start, s), "event record");
+        if (ap.emit_ranges) SDB_HIP(launch_fill_u32(ap.emit_fill, ap.emit_ranges, 0u, s), "range fill");
+        SDB_HIP(launch_slice_partition(sp, plan->slice_grid, s), "slice passes launch");
+        SDB_HIP(launch_slice_agg(ap, std::max(1, di.cus), s), "slice aggregation launch");
+        if (timed) SDB_HIP(hipEventRecord(g_fused_stop, s), "event record");
+    } else if (q->n_fact > 0) {
         int grid = plan->grid;
         if (grid <= 0) {
             st = choose_grid(q, plan, &grid);
@@ -2176,15 +2281,19 @@ SDB_API sdb_status sdb_run_star_query_noalloc(const sdb_query* q, const sdb_plan
                                               int64_t* counts, int64_t n_groups_capacity, void* stream) {
     sdb_status st = check_run(q, plan, sums, counts, n_groups_capacity);
     if (st != SDB_OK) return st;
-    if (plan->run_scratch_bytes < 0 || (uint64_t)plan->run_scratch_bytes > kNoallocScratchBytes)
+    const auto refuse = [&] {
         return fail(SDB_WORKSPACE_TOO_SMALL,
                     "the plan needs %lld bytes of run scratch; the fixed scratch of the allocation-free run holds "
                     "%llu (plan with the global terminal, no per-XCD copies and no table slices)",
                     (long long)plan->run_scratch_bytes, (unsigned long long)kNoallocScratchBytes);
+    };
+    // (a sliced probe's run_scratch_bytes may count its LDS route, which it can do without)
+    const bool beyond = plan->run_scratch_bytes < 0 || (uint64_t)plan->run_scratch_bytes > kNoallocScratchBytes;
+    if (beyond && (plan->run_scratch_bytes < 0 || plan->slice_bits == 0)) return refuse();
     void* fixed = nullptr;
     SDB_HIP(noalloc_scratch(&fixed), "fixed run scratch address");
-    return sdb_run_star_query(q, plan, sums, counts, n_groups_capacity, fixed, (int64_t)kNoallocScratchBytes,
-                              stream);
+    st = sdb_run_star_query(q, plan, sums, counts, n_groups_capacity, fixed, (int64_t)kNoallocScratchBytes, stream);
+    return beyond && st == SDB_WORKSPACE_TOO_SMALL ? refuse() : st;
 }
 
 SDB_API sdb_status sdb_baseline_scratch_bytes(int64_t n_fact, int64_t* bytes) {

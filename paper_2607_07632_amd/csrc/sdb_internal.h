@@ -81,7 +81,20 @@ constexpr int kSliceBlock = 1024;          // threads per block of the count and
 constexpr int kSliceRowsPerThread = 16;    // rows a thread holds per scatter chunk
 constexpr int kSliceChunk = kSliceBlock * kSliceRowsPerThread;   // rows one block sorts in LDS at a time
 constexpr int kSliceMaxGrid = 256;         // one block per compute unit of an MI355X
-static_assert(SDB_MAX_SLICE_BITS <= 10, "scatter LDS holds 3 x 2^10 partition counters");
+// ... and summed slice by slice in LDS (slice_agg_kernel): partitions of the
+// LDS route, its LDS table and how full it gets, rows per work item
+constexpr int kSliceMaxBits = 11;
+static_assert(SDB_MAX_SLICE_BITS <= kSliceMaxBits, "the passes' LDS holds 2^kSliceMaxBits partition counters");
+constexpr int kSliceAggMinBits = 8;        // at least 256 partitions: a work item for every compute unit
+constexpr int kSliceAggHashBits = 15;      // a 16-bit entry number per hash value: 64 KB ...
+constexpr uint32_t kSliceAggEntries = 4608;     // ... of entries of 18 bytes (key, table slot, rows, sum): 81 KB
+constexpr uint32_t kSliceAggItem = 1u << 19;
+constexpr uint32_t kSliceAggMaxGroups = 1024;   // groups summed per block in LDS beside the table (12 bytes each)
+// more groups: the entries leave as records by range of 2^kSliceEmitShift
+// groups, which slice_merge_kernel sums in LDS kSliceEmitChunk at a time
+constexpr int kSliceEmitShift = 12;
+constexpr uint32_t kSliceEmitMaxRanges = 256;
+constexpr uint32_t kSliceEmitChunk = 1u << 16;
 
 // A literal comparison lowered to one unsigned range test over int32:
 // pass  <=>  ((uint32_t)(x - lo) <= span) != negate.
@@ -294,7 +307,7 @@ struct PartParams {
     const uint32_t* rec_gid;
     const void* rec_val;
     int32_t rec_wide;
-    uint32_t pad_;
+    uint32_t chunk_rows;       // records per aggregation work item
     uint32_t* part_hist;       // [q * n_regions + b]: counts, then exclusive offsets within partition q
     uint32_t* part_count;      // records per partition
     uint32_t* part_start;      // n_parts + 1 entries
@@ -305,6 +318,32 @@ struct PartParams {
     uint32_t* item_cnt;
     unsigned long long* sums;
     unsigned long long* counts;
+};
+
+struct v4u_t {
+    uint32_t x, y, z, w;
+};
+
+// The LDS route of the sliced hash probe over the partitioned rows.
+struct SliceAggParams {
+    StageDev st;               // the probe: table, geometry, group-key decoding
+    int32_t bits;              // 2^bits partitions = table slices
+    int32_t agg_kind;
+    const uint32_t* part_start;    // 2^bits + 1 entries
+    const uint32_t* chunk_start;   // work items before each partition; [2^bits] = all
+    const unsigned long long* rec; // {probe key, first operand} a row
+    const int32_t* rec_b;          // second operands (two-column aggregates)
+    uint32_t n_groups;
+    uint32_t lds_groups;       // n_groups where a block sums its groups in LDS, else 0
+    int32_t xcd_copies;
+    uint32_t emit_ranges;      // > 0: entries leave as records, emit_cap a range of groups
+    uint32_t emit_cap;
+    uint32_t pad_;
+    uint32_t* emit_fill;       // records claimed per range (may pass emit_cap), zeroed by the host
+    v4u_t* emit;               // {group, rows, low and high word of the sum}: [range * emit_cap + i]
+    unsigned long long* sums;
+    unsigned long long* counts;
+    unsigned long long* xtab;  // per-XCD interleaved {sum, count} copies, or null
 };
 
 // Count and scatter passes of the sliced hash probe. Block b of the grid
@@ -327,6 +366,9 @@ struct SliceParams {
     int32_t* out_key;          // partitioned keys and values, all passing rows
     int32_t* out_val;
     int32_t* out_val2;         // val2_col >= 0: the second operands
+    unsigned long long* out_rec;   // LDS route: {key, value} pairs in place of out_key and out_val
+    uint32_t item_rows;        // LDS route: rows per work item (chunk_start)
+    uint32_t pad_;
     // tile order of the fused launch over them: its tiles of tile_rows rows;
     // XCD x (x = q mod 8) walks the tiles whose first row lies in partition q
     int64_t tile_rows;
@@ -391,6 +433,8 @@ hipError_t launch_finalize(const FinalizeParams& fp, hipStream_t s);
 hipError_t launch_part_passes(const PartParams& pp, hipStream_t s);
 // count pass, per-partition offsets, scatter pass over `grid` blocks
 hipError_t launch_slice_partition(const SliceParams& sp, int grid, hipStream_t s);
+// the LDS route's aggregation of the partitioned rows (adds into the outputs)
+hipError_t launch_slice_agg(const SliceAggParams& ap, int grid, hipStream_t s);
 
 // the fixed run scratch of sdb_run_star_query_noalloc: its device address on
 // the calling thread's current device

@@ -1098,7 +1098,7 @@ __global__ void __launch_bounds__(1024) part_scan_kernel(PartParams pp) {
     for (uint32_t base = 0; base < pp.n_parts; base += 1024u) {
         const uint32_t i = base + threadIdx.x;
         const uint32_t vr = i < pp.n_parts ? pp.part_count[i] : 0u;
-        const uint32_t vc = (vr + (uint32_t)kPartChunk - 1u) / (uint32_t)kPartChunk;
+        const uint32_t vc = vr / pp.chunk_rows + (vr % pp.chunk_rows != 0u ? 1u : 0u);
         buf_r[threadIdx.x] = vr;
         buf_c[threadIdx.x] = vc;
         __syncthreads();
@@ -1615,6 +1615,210 @@ __global__ void __launch_bounds__(kSliceBlock) slice_scatter_kernel(SliceParams 
     }
 }
 
+// Rows 4 * t .. 4 * t + 3 of the n rows at col (16-byte aligned): one 128-bit
+// load, or row by row in a last partial group (0 past its end).
+__device__ __forceinline__ v4i slice_load_group(const int32_t* col, uint32_t t, uint32_t n) {
+    v4i x = {0, 0, 0, 0};
+    if (4u * t + 3u < n) {
+        x = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(col) + t);
+    } else {
+        if (4u * t < n) x.x = __builtin_nontemporal_load(col + 4u * t);
+        if (4u * t + 1u < n) x.y = __builtin_nontemporal_load(col + 4u * t + 1u);
+        if (4u * t + 2u < n) x.z = __builtin_nontemporal_load(col + 4u * t + 2u);
+    }
+    return x;
+}
+
+// A thread's G groups of four rows (group i at row 4 * (i * kSliceBlock +
+// threadIdx.x)) of the n rows at col; groups without a live row may be left out.
+template <int G>
+__device__ __forceinline__ void slice_load_values(const int32_t* col, uint32_t n, uint32_t live, int32_t (&v)[4 * G]) {
+    if (n == 4u * G * kSliceBlock) {   // a whole chunk: no checks
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            const v4i x =
+                __builtin_nontemporal_load(reinterpret_cast<const v4i*>(col) + ((uint32_t)i * kSliceBlock + threadIdx.x));
+            v[4 * i] = x.x;
+            v[4 * i + 1] = x.y;
+            v[4 * i + 2] = x.z;
+            v[4 * i + 3] = x.w;
+        }
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+        v4i x = {0, 0, 0, 0};
+        if ((live >> (4 * i)) & 0xFu) x = slice_load_group(col, (uint32_t)i * kSliceBlock + threadIdx.x, n);
+        v[4 * i] = x.x;
+        v[4 * i + 1] = x.y;
+        v[4 * i + 2] = x.z;
+        v[4 * i + 3] = x.w;
+    }
+}
+
+// A thread's rows of the chunk of n rows at c0 (at most 4 * G * kSliceBlock):
+// G groups of four, group i at row 4 * (i * kSliceBlock + threadIdx.x). Their
+// keys, and in the result's bits which of them are below n and pass every fact
+// predicate.
+template <int G>
+__device__ __forceinline__ uint32_t slice_load_live(const SliceParams& sp, int64_t c0, uint32_t n, int32_t (&k)[4 * G]) {
+    uint32_t live = 0u;
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+        const uint32_t r = 4u * ((uint32_t)i * kSliceBlock + threadIdx.x);
+        const uint32_t left = n > r ? min(n - r, 4u) : 0u;
+        live |= ((1u << left) - 1u) << (4 * i);
+    }
+    for (int pi = 0; pi < sp.n_preds; ++pi) {
+        const int32_t* col = sp.cols[sp.pred_col[pi]] + c0;
+        const RangeTest t = sp.pred[pi];
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            if (!((live >> (4 * i)) & 0xFu)) continue;
+            const v4i x = slice_load_group(col, (uint32_t)i * kSliceBlock + threadIdx.x, n);
+            const uint32_t ok = (range_pass(t, x.x) ? 1u : 0u) | (range_pass(t, x.y) ? 2u : 0u) |
+                                (range_pass(t, x.z) ? 4u : 0u) | (range_pass(t, x.w) ? 8u : 0u);
+            live &= ~((ok ^ 0xFu) << (4 * i));
+        }
+    }
+    slice_load_values<G>(sp.cols[sp.key_col] + c0, n, live, k);
+    return live;
+}
+
+// Count pass of the LDS route (slice_count_kernel's counts), the next chunk's
+// loads issued before this one is counted. Bound by the read of the columns.
+__global__ void __launch_bounds__(kSliceBlock) slice_count_rec_kernel(SliceParams sp) {
+    constexpr int G = 4;
+    constexpr int64_t CHUNK = 4 * G * kSliceBlock;
+    __shared__ uint32_t lh[4 << kSliceMaxBits];
+    const uint32_t P = 1u << sp.bits;
+    for (uint32_t q = threadIdx.x; q < 4u * P; q += kSliceBlock) lh[q] = 0u;
+    __syncthreads();
+    uint32_t* mine = lh + (threadIdx.x & 3u);
+    const int64_t r0 = (int64_t)blockIdx.x * sp.rows_per_block;
+    const int64_t r1 = min(sp.n, r0 + sp.rows_per_block);
+    int32_t k[4 * G], next[4 * G];
+    uint32_t live = 0u, next_live = 0u;
+    if (r0 < r1) live = slice_load_live<G>(sp, r0, (uint32_t)min(r1 - r0, CHUNK), k);
+    for (int64_t c0 = r0; c0 < r1; c0 += CHUNK) {
+        if (c0 + CHUNK < r1)
+            next_live = slice_load_live<G>(sp, c0 + CHUNK, (uint32_t)min(r1 - c0 - CHUNK, CHUNK), next);
+#pragma unroll
+        for (int i = 0; i < 4 * G; ++i)
+            if ((live >> i) & 1u) atomicAdd(&mine[4u * slice_of(k[i], sp.bits)], 1u);
+#pragma unroll
+        for (int i = 0; i < 4 * G; ++i) k[i] = next[i];
+        live = next_live;
+    }
+    __syncthreads();
+    for (uint32_t q = threadIdx.x; q < P; q += kSliceBlock)
+        sp.hist[(uint64_t)q * gridDim.x + blockIdx.x] = lh[4u * q] + lh[4u * q + 1u] + lh[4u * q + 2u] + lh[4u * q + 3u];
+}
+
+// Writes the n rows of an LDS window that starts at place w0 of its chunk.
+template <bool TWO>
+__device__ __forceinline__ void slice_write_window(const SliceParams& sp, const unsigned long long* srec,
+                                                   const int32_t* sval2, const uint32_t* lcur, uint32_t w0, uint32_t n) {
+    for (uint32_t i = threadIdx.x; i < n; i += kSliceBlock) {
+        const unsigned long long rec = srec[i];
+        const uint32_t dest = lcur[slice_of((int32_t)(uint32_t)rec, sp.bits)] + w0 + i;
+        if ((int64_t)dest < sp.n) {   // always: both passes count the same rows
+            sp.out_rec[dest] = rec;
+            if constexpr (TWO) sp.out_val2[dest] = sval2[i];
+        }
+    }
+}
+
+// Scatter pass of the LDS route, whose partitions are many (up to 2,048): the
+// longer the chunk a block sorts at a time, the longer the runs it writes, so
+// a chunk's rows (4 * G a thread) stay in registers and only WINDOW of them
+// at a time pass through LDS in partition order. Bound by the runs' partial
+// lines. The next chunk's loads are issued before the last window is written.
+template <int G, bool TWO>
+__global__ void __launch_bounds__(kSliceBlock) slice_scatter_rec_kernel(SliceParams sp) {
+    constexpr int RPT = 4 * G, CHUNK = RPT * kSliceBlock;
+    constexpr uint32_t WINDOW = TWO ? 8192u : 16384u;
+    static_assert(CHUNK <= 65536, "16-bit places in a chunk");
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    __shared__ uint32_t wtmp[kSliceBlock / 64];
+    unsigned long long* srec = reinterpret_cast<unsigned long long*>(smem);
+    int32_t* sval2 = reinterpret_cast<int32_t*>(srec + WINDOW);   // TWO only
+    const uint32_t P = 1u << sp.bits;
+    uint32_t* lcnt = reinterpret_cast<uint32_t*>(sval2 + (TWO ? WINDOW : 0u));
+    uint32_t* lstart = lcnt + P;
+    uint32_t* lcur = lstart + P;      // next position in the partition, less lstart once that is known
+    for (uint32_t q = threadIdx.x; q < P; q += kSliceBlock) {
+        lcur[q] = sp.part_start[q] + sp.hist[(uint64_t)q * gridDim.x + blockIdx.x];
+        lcnt[q] = 0u;
+    }
+    __syncthreads();
+    const int64_t r0 = (int64_t)blockIdx.x * sp.rows_per_block;
+    const int64_t r1 = min(sp.n, r0 + sp.rows_per_block);
+    const int32_t* val = sp.cols[sp.val_col];
+    const int32_t* val2 = sp.cols[TWO ? sp.val2_col : sp.val_col];
+    int32_t k[RPT], v[RPT], v2[TWO ? RPT : 4];
+    uint32_t live = 0u;
+    const auto load = [&](int64_t at) {
+        const uint32_t n = (uint32_t)min(r1 - at, (int64_t)CHUNK);
+        live = slice_load_live<G>(sp, at, n, k);
+        slice_load_values<G>(val + at, n, live, v);
+        if constexpr (TWO) slice_load_values<G>(val2 + at, n, live, v2);
+    };
+    if (r0 < r1) load(r0);
+    for (int64_t c0 = r0; c0 < r1; c0 += CHUNK) {
+        // each row's rank in its partition, then its place in partition order, two to a register
+        uint32_t place[RPT / 2];
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {
+            uint32_t r = 0u;
+            if ((live >> i) & 1u) r = atomicAdd(&lcnt[slice_of(k[i], sp.bits)], 1u);
+            place[i / 2] = (i & 1) ? place[i / 2] | (r << 16) : r;
+            if (G > 4 && i % 8 == 7) __builtin_amdgcn_sched_barrier(0);   // at most 8 results in registers
+        }
+        // (the partitions are worked out again below rather than kept in registers)
+#pragma unroll
+        for (int i = 0; i < (G > 4 ? RPT : 0); ++i) asm volatile("" : "+v"(k[i]));
+        __syncthreads();
+        const uint32_t cn = __builtin_amdgcn_readfirstlane(block_scan_any(lcnt, lstart, P, 0u, wtmp));
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {
+            const uint32_t s = lstart[slice_of(k[i], sp.bits)];
+            place[i / 2] += (i & 1) ? s << 16 : s;
+            if (G > 4 && i % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+        }
+        for (uint32_t q = threadIdx.x; q < P; q += kSliceBlock) lcur[q] -= lstart[q];
+        uint32_t w0 = 0u;
+        for (;;) {
+#pragma unroll
+            for (int i = 0; i < RPT; ++i) {
+                const uint32_t at = ((place[i / 2] >> ((i & 1) * 16)) & 0xFFFFu) - w0;
+                if (((live >> i) & 1u) && at < WINDOW) {
+                    srec[at] = ((unsigned long long)(uint32_t)v[i] << 32) | (uint32_t)k[i];
+                    if constexpr (TWO) sval2[at] = v2[i];
+                }
+            }
+            if (w0 + WINDOW >= cn) break;
+            __syncthreads();
+            slice_write_window<TWO>(sp, srec, sval2, lcur, w0, WINDOW);
+            __syncthreads();
+            w0 += WINDOW;
+        }
+        if (c0 + CHUNK < r1) load(c0 + CHUNK);
+        __syncthreads();
+        slice_write_window<TWO>(sp, srec, sval2, lcur, w0, cn - w0);
+        __syncthreads();
+        for (uint32_t q = threadIdx.x; q < P; q += kSliceBlock) {
+            lcur[q] += lstart[q] + lcnt[q];
+            lcnt[q] = 0u;
+        }
+        __syncthreads();
+    }
+}
+
+size_t slice_scatter_rec_lds_bytes(uint32_t n_parts, bool two) {
+    return (two ? 8192u * 12u : 16384u * 8u) + (size_t)n_parts * 12u;
+}
+
 // The tile order of the fused launch over the partitioned rows. Loop index t
 // runs on block t mod grid, which the dispatcher places on XCD t mod 8 (the
 // grids here are multiples of 8); giving XCD x only the tiles whose first row
@@ -1667,9 +1871,11 @@ size_t slice_scatter_lds_bytes(uint32_t n_parts, bool two) {
 }
 
 hipError_t launch_slice_partition(const SliceParams& sp, int grid, hipStream_t s) {
-    if (sp.bits < 1 || sp.bits > SDB_MAX_SLICE_BITS || grid < 1) return hipErrorInvalidValue;
+    if (sp.bits < 1 || sp.bits > kSliceMaxBits || grid < 1) return hipErrorInvalidValue;
     const uint32_t P = 1u << sp.bits;
-    hipLaunchKernelGGL(slice_count_kernel, dim3(grid), dim3(kSliceBlock), 0, s, sp);
+    if (!sp.out_rec && sp.bits > SDB_MAX_SLICE_BITS) return hipErrorInvalidValue;
+    if (sp.out_rec) hipLaunchKernelGGL(slice_count_rec_kernel, dim3(grid), dim3(kSliceBlock), 0, s, sp);
+    else hipLaunchKernelGGL(slice_count_kernel, dim3(grid), dim3(kSliceBlock), 0, s, sp);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     PartParams pp;
@@ -1680,13 +1886,27 @@ hipError_t launch_slice_partition(const SliceParams& sp, int grid, hipStream_t s
     pp.part_count = sp.part_count;
     pp.part_start = sp.part_start;
     pp.chunk_start = sp.chunk_start;
+    pp.chunk_rows = sp.out_rec ? sp.item_rows : (uint32_t)kPartChunk;
     hipLaunchKernelGGL(part_offsets_kernel, dim3(P), dim3(256), 0, s, pp);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(part_scan_kernel, dim3(1), dim3(1024), 0, s, pp);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (sp.val2_col >= 0)
+    const bool two = sp.val2_col >= 0;
+    if (sp.out_rec && two)
+        hipLaunchKernelGGL((slice_scatter_rec_kernel<4, true>), dim3(grid), dim3(kSliceBlock),
+                           slice_scatter_rec_lds_bytes(P, true), s, sp);
+    // chunks of 32,768 rows where 16,384 would leave runs of at most 8 rows and a
+    // block has many chunks (2,048 partitions: 600M rows 3.67 against 4.18 ms, but
+    // 40M rows in 256 partitions 190 against 134 us)
+    else if (sp.out_rec && sp.bits >= 11 && sp.rows_per_block >= 16 * 32768)
+        hipLaunchKernelGGL((slice_scatter_rec_kernel<8, false>), dim3(grid), dim3(kSliceBlock),
+                           slice_scatter_rec_lds_bytes(P, false), s, sp);
+    else if (sp.out_rec)
+        hipLaunchKernelGGL((slice_scatter_rec_kernel<4, false>), dim3(grid), dim3(kSliceBlock),
+                           slice_scatter_rec_lds_bytes(P, false), s, sp);
+    else if (two)
         hipLaunchKernelGGL((slice_scatter_kernel<kSliceRowsPerThreadTwo, true>), dim3(grid), dim3(kSliceBlock),
                            slice_scatter_lds_bytes(P, true), s, sp);
     else
@@ -1704,6 +1924,391 @@ hipError_t launch_slice_partition(const SliceParams& sp, int grid, hipStream_t s
         const int g = (int)std::min<uint64_t>(1024u, std::max<uint64_t>(1u, (phys + 255u) / 256u));
         hipLaunchKernelGGL(slice_tile_map_kernel, dim3(g), dim3(256), 0, s, sp);
     }
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// the LDS route of the sliced hash probe
+// ---------------------------------------------------------------------------
+
+constexpr uint32_t kAggHashes = 1u << kSliceAggHashBits;
+constexpr uint32_t kAggFree = 0xFFFFu;   // hash value without an entry
+static_assert(kSliceAggEntries < kAggFree, "16-bit entry numbers");
+
+// The LDS table of a slice's passing keys: kAggHashes 16-bit entry numbers,
+// looked up from the hash bits below the slice's with linear probing (at most
+// 4,608 of 32,768 are taken, so most rows end at the first), and the entries.
+struct SliceTable {
+    uint16_t* at;              // kAggHashes entry numbers or kAggFree
+    uint32_t* key;             // kSliceAggEntries each
+    uint16_t* slot;            // where the key stands: table slots from the slice's (or round's) first on
+    uint32_t* rows;
+    unsigned long long* sum;
+};
+
+__device__ __forceinline__ uint32_t slice_hash(uint32_t key, int bits) {
+    return ((key * 0x9E3779B1u) << bits) >> (32 - kSliceAggHashBits);
+}
+
+// The entry of `key`, or kAggFree, from hash value h on.
+__device__ __forceinline__ uint32_t slice_find(const SliceTable& t, uint32_t key, uint32_t h) {
+    uint32_t e = t.at[h];
+    while (e != kAggFree && t.key[e] != key) {
+        h = (h + 1u) & (kAggHashes - 1u);
+        e = t.at[h];
+    }
+    return e;
+}
+
+// A table slot read for slice q: whether it holds a passing row of the slice.
+__device__ __forceinline__ bool slice_slot_passes(unsigned long long slot, uint32_t q, int bits) {
+    const uint32_t enc = (uint32_t)(slot >> 32);
+    return enc != 0u && enc != 0xFFFFFFFFu && slice_of((int32_t)(uint32_t)slot, bits) == q;
+}
+
+// Puts the wave's slots that hold a passing row of slice q into the LDS table
+// (as slot number `at`), as long as entries are free; *n counts them all. The
+// whole wave calls it together.
+__device__ __forceinline__ void slice_put(unsigned long long slot, uint32_t at, uint32_t q, int bits,
+                                          const SliceTable& t, uint32_t* n) {
+    const bool pass = slice_slot_passes(slot, q, bits);
+    const uint32_t lane = threadIdx.x & 63u;
+    const unsigned long long m = __ballot(pass);
+    uint32_t e = 0;
+    if (lane == 0 && m) e = atomicAdd(n, (uint32_t)__popcll(m));
+    e = __shfl(e, 0, 64) + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+    if (pass && e < kSliceAggEntries) {
+        const uint32_t key = (uint32_t)slot;
+        t.key[e] = key;
+        t.slot[e] = (uint16_t)at;
+        t.rows[e] = 0u;
+        t.sum[e] = 0ull;
+        // the first free hash value from the key's on takes the entry
+        uint32_t* words = reinterpret_cast<uint32_t*>(t.at);
+        uint32_t h = slice_hash(key, bits);
+        uint32_t old = words[h >> 1];
+        for (;;) {
+            const uint32_t sh = (h & 1u) * 16u;
+            if (((old >> sh) & 0xFFFFu) != kAggFree) {
+                h = (h + 1u) & (kAggHashes - 1u);
+                old = words[h >> 1];
+                continue;
+            }
+            const uint32_t got = atomicCAS(&words[h >> 1], old, (old & ~(0xFFFFu << sh)) | (e << sh));
+            if (got == old) break;
+            old = got;
+        }
+    }
+}
+
+// Puts the passing rows among table slots [lo, hi), counted from the slice's
+// first, into the LDS table. The whole block calls it together.
+__device__ __forceinline__ void slice_fill_table(const SliceAggParams& ap, uint32_t q, uint32_t lo, uint32_t hi,
+                                                 const SliceTable& t, uint32_t* n) {
+    constexpr int U = 16;
+    const unsigned long long* tab = static_cast<const unsigned long long*>(ap.st.map);
+    const uint32_t base = q * (ap.st.nslots >> ap.bits);
+    for (uint32_t i0 = lo; i0 < hi; i0 += U * blockDim.x) {
+        unsigned long long slot[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t i = i0 + (uint32_t)u * blockDim.x + threadIdx.x;
+            slot[u] = i < hi ? tab[(base + i) & ap.st.hmask] : 0ull;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            slice_put(slot[u], i0 + (uint32_t)u * blockDim.x + threadIdx.x - lo, q, ap.bits, t, n);
+    }
+}
+
+// Adds rows [r0, r1) of a partition to the entries of their keys. A thread
+// takes kAggPairs pairs of rows a step (16-byte loads), the next step's loads
+// issued before this one's lookups; the first lookups of its rows are made
+// together, and the rows that met another key go on one by one.
+constexpr int kAggPairs = 3;
+
+template <bool TWO>
+__device__ __forceinline__ void slice_load_pairs(const unsigned long long* rec, const int32_t* rec_b, uint32_t at,
+                                                 uint32_t n, u64x2 (&x)[kAggPairs], unsigned long long (&w)[kAggPairs]) {
+#pragma unroll
+    for (int k = 0; k < kAggPairs; ++k) {
+        uint32_t i = at + 2u * ((uint32_t)k * 1024u + threadIdx.x);
+        i = i < n ? i : 0u;   // past the last row: any pair of the item
+        x[k] = __builtin_nontemporal_load(reinterpret_cast<const u64x2*>(rec + i));
+        if (TWO) w[k] = __builtin_nontemporal_load(reinterpret_cast<const unsigned long long*>(rec_b + i));
+    }
+}
+
+template <bool TWO>
+__device__ __forceinline__ void slice_add_rows(const SliceAggParams& ap, uint32_t r0, uint32_t r1,
+                                               const SliceTable& t) {
+    constexpr int U = 2 * kAggPairs;
+    constexpr uint32_t kStep = U * 1024u;
+    if (r0 >= r1) return;
+    const uint32_t skip = r0 & 1u;   // pairs start at even rows
+    const uint32_t n = r1 - r0 + skip;
+    const unsigned long long* rec = ap.rec + (r0 - skip);
+    const int32_t* rec_b = TWO ? ap.rec_b + (r0 - skip) : nullptr;
+    u64x2 x[kAggPairs];
+    unsigned long long w[kAggPairs];
+    slice_load_pairs<TWO>(rec, rec_b, 0u, n, x, w);
+    for (uint32_t at = 0; at < n; at += kStep) {
+        uint32_t key[U], h[U], e[U], k[U];
+        const bool full = at >= skip && at + kStep <= n;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            key[u] = (uint32_t)((u & 1) ? x[u >> 1].y : x[u >> 1].x);
+            h[u] = slice_hash(key[u], ap.bits);
+            e[u] = t.at[h[u]];
+        }
+        long long v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const unsigned long long r = (u & 1) ? x[u >> 1].y : x[u >> 1].x;
+            v[u] = (long long)(int32_t)(uint32_t)(r >> 32);
+            if (TWO) {
+                const long long y = (long long)(int32_t)(uint32_t)((u & 1) ? w[u >> 1] >> 32 : w[u >> 1]);
+                v[u] = ap.agg_kind == SDB_AGG_MUL ? v[u] * y : (ap.agg_kind == SDB_AGG_SUB ? v[u] - y : v[u] + y);
+            }
+        }
+        if (at + kStep < n) slice_load_pairs<TWO>(rec, rec_b, at + kStep, n, x, w);
+        if (!full) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t i = at + 2u * ((uint32_t)(u >> 1) * 1024u + threadIdx.x) + (u & 1);
+                if (i < skip || i >= n) e[u] = kAggFree;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) k[u] = t.key[e[u] != kAggFree ? e[u] : 0u];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (e[u] != kAggFree && k[u] != key[u]) e[u] = slice_find(t, key[u], (h[u] + 1u) & (kAggHashes - 1u));
+            if (e[u] != kAggFree) {
+                atomicAdd(&t.rows[e[u]], 1u);
+                atomicAdd(&t.sum[e[u]], (unsigned long long)v[u]);
+            }
+        }
+    }
+}
+
+__device__ __forceinline__ void slice_clear_table(const SliceTable& t) {
+    v4u* w = reinterpret_cast<v4u*>(t.at);
+    for (uint32_t k = threadIdx.x; k < kAggHashes / 8u; k += blockDim.x) w[k] = v4u{~0u, ~0u, ~0u, ~0u};
+}
+
+__device__ __forceinline__ unsigned long long* xcd_copy(const SliceAggParams& ap) {
+    return ap.xcd_copies > 0 ? ap.xtab + 2ull * ap.n_groups * (xcc_id() & (uint32_t)(ap.xcd_copies - 1)) : nullptr;
+}
+
+// Adds a sum over `rows` rows to group g of the outputs, or of this XCD's copy.
+__device__ __forceinline__ void add_group_total(const SliceAggParams& ap, unsigned long long* xt, uint32_t g,
+                                                unsigned long long sum, unsigned long long rows) {
+    atomicAdd(xt ? &xt[2ull * g] : &ap.sums[g], sum);
+    atomicAdd(xt ? &xt[2ull * g + 1u] : &ap.counts[g], rows);
+}
+
+// Sums the partitioned rows by dimension row before the join: a work item (at
+// most kSliceAggItem rows of partition q) loads the passing rows of table
+// slice q into an LDS table, adds every row's value and count to its key's
+// entry (rows whose key is not there die: misses and filtered rows alike), and
+// then adds each entry once to its group. A passing key's rows so cost two LDS
+// atomics each and its group one update per work item, instead of a record
+// (or an atomic) per row. With few groups (lds_groups) the block keeps them in
+// LDS and flushes them once; with more, the entries leave as records by range
+// of groups (what is past a range's capacity, and the rest, with global
+// atomics).
+// Keys of a slice stand between its first slot and the first empty slot past
+// its end (linear probing), so that is the range of slots read. Should more
+// than kSliceAggEntries of them pass (keys that hash unevenly), the rows are
+// gone through once for every kSliceAggEntries slots.
+template <bool TWO>
+__global__ void __launch_bounds__(1024) slice_agg_kernel(SliceAggParams kernel_args) {
+    (void)kernel_args;
+    const SliceAggParams& ap = *(const SliceAggParams*)__builtin_amdgcn_kernarg_segment_ptr();
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    __shared__ uint32_t s_len, s_n, s_q;
+    __shared__ uint32_t s_emit[kSliceEmitMaxRanges], s_emit_at[kSliceEmitMaxRanges];
+    for (uint32_t r = threadIdx.x; r < kSliceEmitMaxRanges; r += blockDim.x) s_emit[r] = 0u;
+    SliceTable t;
+    t.sum = reinterpret_cast<unsigned long long*>(smem);
+    t.at = reinterpret_cast<uint16_t*>(t.sum + kSliceAggEntries);
+    t.key = reinterpret_cast<uint32_t*>(t.at + kAggHashes);
+    t.rows = t.key + kSliceAggEntries;
+    t.slot = reinterpret_cast<uint16_t*>(t.rows + kSliceAggEntries);
+    unsigned long long* gsum = reinterpret_cast<unsigned long long*>(t.slot + kSliceAggEntries);
+    uint32_t* gcnt = reinterpret_cast<uint32_t*>(gsum + ap.lds_groups);
+    const StageDev& S = ap.st;
+    const unsigned long long* tab = static_cast<const unsigned long long*>(S.map);
+    const uint32_t P = 1u << ap.bits, per = S.nslots >> ap.bits;
+    for (uint32_t g = threadIdx.x; g < ap.lds_groups; g += blockDim.x) {
+        gsum[g] = 0ull;
+        gcnt[g] = 0u;
+    }
+    unsigned long long* xt = xcd_copy(ap);
+    const uint32_t n_items = ap.chunk_start[P];
+    for (uint32_t c = blockIdx.x; c < n_items; c += gridDim.x) {
+        // partition holding work item c
+        for (uint32_t i = threadIdx.x; i < P; i += blockDim.x)
+            if (ap.chunk_start[i] <= c && c < ap.chunk_start[i + 1]) s_q = i;
+        if (threadIdx.x == 0) s_n = 0u;
+        slice_clear_table(t);
+        __syncthreads();
+        const uint32_t q = __builtin_amdgcn_readfirstlane(s_q);
+        const uint32_t base = q * per;
+        slice_fill_table(ap, q, 0u, per, t, &s_n);
+        if (threadIdx.x < 64u) {
+            // the slots past the slice's up to the first empty one
+            for (uint32_t off = per;; off += 64u) {
+                const uint32_t i = off + threadIdx.x;
+                const unsigned long long slot = i < S.nslots ? tab[(base + i) & S.hmask] : 0ull;
+                const unsigned long long m = __ballot((slot >> 32) == 0ull);
+                const uint32_t end = m ? (uint32_t)__ffsll((long long)m) - 1u : 64u;
+                slice_put(threadIdx.x < end ? slot : 0ull, i, q, ap.bits, t, &s_n);
+                if (m) {
+                    if (threadIdx.x == 0) s_len = off + end;
+                    break;
+                }
+            }
+        }
+        __syncthreads();
+        const uint32_t len = __builtin_amdgcn_readfirstlane(s_len);
+        const uint32_t n_pass = __builtin_amdgcn_readfirstlane(s_n);
+        // one round over the rows when the slice's entries fit the table and
+        // their slot numbers 16 bits, else one for every kSliceAggEntries slots
+        const bool one = n_pass <= kSliceAggEntries && len <= 65536u;
+        const bool none = n_pass == 0u;
+        // the partition's rows in equal shares over its work items
+        const uint32_t p0 = ap.part_start[q], p1 = ap.part_start[q + 1];
+        const uint32_t c0 = ap.chunk_start[q], share = (p1 - p0 - 1u) / (ap.chunk_start[q + 1] - c0) + 1u;
+        const uint32_t r0 = p0 + min((c - c0) * share, p1 - p0);
+        const uint32_t r1 = min(p1 - r0, share) + r0;
+        for (uint32_t lo = 0; lo < len && !none;) {
+            const uint32_t hi = one ? len : min(len, lo + kSliceAggEntries);
+            if (!one) {
+                __syncthreads();
+                slice_clear_table(t);
+                if (threadIdx.x == 0) s_n = 0u;
+                __syncthreads();
+                slice_fill_table(ap, q, lo, hi, t, &s_n);
+                __syncthreads();
+            }
+            const uint32_t n_entries = one ? n_pass : __builtin_amdgcn_readfirstlane(s_n);
+            slice_add_rows<TWO>(ap, r0, r1, t);
+            __syncthreads();
+            // every entry once into its group; its code from the table slot
+            constexpr int E = (int)((kSliceAggEntries + 1023u) / 1024u);
+            {
+                uint32_t g[E], rows[E], rank[E];
+                unsigned long long sum[E];
+#pragma unroll
+                for (int u = 0; u < E; ++u) {
+                    const uint32_t e = (uint32_t)u * 1024u + threadIdx.x;
+                    rows[u] = e < n_entries ? t.rows[e] : 0u;
+                    g[u] = 0u;
+                    if (rows[u]) g[u] = (uint32_t)(tab[(base + lo + t.slot[e]) & S.hmask] >> 32) - 1u;
+                }
+#pragma unroll
+                for (int u = 0; u < E; ++u) {
+                    if (!rows[u]) continue;
+                    sum[u] = t.sum[(uint32_t)u * 1024u + threadIdx.x];
+                    g[u] = S.gk_mode == GK_ONE ? g[u] * S.gk_stride[0]
+                         : S.gk_mode == GK_GENERAL ? code_contribution(S, g[u]) : 0u;
+                }
+                if (ap.emit_ranges) {
+                    // ranks within the ranges, one claim per range for the block's entries
+#pragma unroll
+                    for (int u = 0; u < E; ++u)
+                        if (rows[u]) rank[u] = atomicAdd(&s_emit[g[u] >> kSliceEmitShift], 1u);
+                    __syncthreads();
+                    for (uint32_t r = threadIdx.x; r < ap.emit_ranges; r += blockDim.x) {
+                        const uint32_t n = s_emit[r];
+                        s_emit[r] = 0u;
+                        s_emit_at[r] = n ? atomicAdd(&ap.emit_fill[r], n) : 0u;
+                    }
+                    __syncthreads();
+                }
+#pragma unroll
+                for (int u = 0; u < E; ++u) {
+                    if (!rows[u]) continue;
+                    if (ap.lds_groups) {
+                        atomicAdd(&gsum[g[u]], sum[u]);
+                        atomicAdd(&gcnt[g[u]], rows[u]);
+                        continue;
+                    }
+                    if (ap.emit_ranges) {
+                        const uint32_t r = g[u] >> kSliceEmitShift;
+                        const uint32_t at = s_emit_at[r] + rank[u];
+                        if (at < ap.emit_cap) {
+                            const v4u rec = {g[u], rows[u], (uint32_t)sum[u], (uint32_t)(sum[u] >> 32)};
+                            reinterpret_cast<v4u*>(ap.emit)[(uint64_t)r * ap.emit_cap + at] = rec;
+                            continue;
+                        }
+                    }
+                    add_group_total(ap, xt, g[u], sum[u], rows[u]);
+                }
+            }
+            lo = hi;
+        }
+        __syncthreads();
+    }
+    __syncthreads();
+    for (uint32_t g = threadIdx.x; g < ap.lds_groups; g += blockDim.x)
+        if (gcnt[g]) {
+            atomicAdd(&ap.sums[g], gsum[g]);
+            atomicAdd(&ap.counts[g], (unsigned long long)gcnt[g]);
+        }
+}
+
+// One block per kSliceEmitChunk records of a range of groups (block
+// x: chunk, y: range): sums them in LDS, then adds the chunk's groups.
+__global__ void __launch_bounds__(1024) slice_merge_kernel(SliceAggParams kernel_args) {
+    (void)kernel_args;
+    const SliceAggParams& ap = *(const SliceAggParams*)__builtin_amdgcn_kernarg_segment_ptr();
+    constexpr uint32_t G = 1u << kSliceEmitShift;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    unsigned long long* lsum = reinterpret_cast<unsigned long long*>(smem);
+    unsigned long long* lrows = lsum + G;
+    const uint32_t r = blockIdx.y, n = min(ap.emit_fill[r], ap.emit_cap);
+    const uint32_t i0 = blockIdx.x * kSliceEmitChunk;
+    if (i0 >= n) return;
+    const uint32_t i1 = min(n - i0, kSliceEmitChunk) + i0, g0 = r << kSliceEmitShift;
+    for (uint32_t k = threadIdx.x; k < 2u * G; k += blockDim.x) lsum[k] = 0ull;
+    __syncthreads();
+    const v4u* rec = reinterpret_cast<const v4u*>(ap.emit) + (uint64_t)r * ap.emit_cap;
+    constexpr int U = 8;
+    for (uint32_t j0 = i0; j0 < i1; j0 += U * blockDim.x) {
+        v4u x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t i = j0 + (uint32_t)u * blockDim.x + threadIdx.x;
+            x[u] = i < i1 ? __builtin_nontemporal_load(rec + i) : v4u{g0, 0u, 0u, 0u};
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (x[u].y) {
+                atomicAdd(&lsum[x[u].x - g0], ((unsigned long long)x[u].w << 32) | x[u].z);
+                atomicAdd(&lrows[x[u].x - g0], (unsigned long long)x[u].y);
+            }
+    }
+    __syncthreads();
+    unsigned long long* xt = xcd_copy(ap);
+    for (uint32_t k = threadIdx.x; k < G; k += blockDim.x)
+        if (lrows[k]) add_group_total(ap, xt, g0 + k, lsum[k], lrows[k]);
+}
+
+hipError_t launch_slice_agg(const SliceAggParams& ap, int grid, hipStream_t s) {
+    if (ap.bits < 1 || ap.bits > kSliceMaxBits || grid < 1 || ap.lds_groups > kSliceAggMaxGroups ||
+        ap.emit_ranges > kSliceEmitMaxRanges)
+        return hipErrorInvalidValue;
+    const size_t lds = (size_t)kSliceAggEntries * 18u + (size_t)kAggHashes * 2u + (size_t)ap.lds_groups * 12u;
+    if (ap.rec_b) hipLaunchKernelGGL(slice_agg_kernel<true>, dim3(grid), dim3(1024), lds, s, ap);
+    else hipLaunchKernelGGL(slice_agg_kernel<false>, dim3(grid), dim3(1024), lds, s, ap);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !ap.emit_ranges) return e;
+    const uint32_t chunks = (ap.emit_cap + kSliceEmitChunk - 1u) / kSliceEmitChunk;
+    hipLaunchKernelGGL(slice_merge_kernel, dim3(chunks, ap.emit_ranges), dim3(1024),
+                       (size_t)16u << kSliceEmitShift, s, ap);
     return hipGetLastError();
 }
 

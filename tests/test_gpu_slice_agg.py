@@ -1,0 +1,121 @@
+"""The sliced hash probe's LDS route (rows partitioned by table slice, summed
+by dimension row in LDS) where it can go wrong: slices that overfill the LDS
+table, runs past a slice's end and around the table's, hot keys split over
+work items, every way the groups leave, and a scratch that only holds the
+route through L2. Everything is compared with the oracle, exactly."""
+
+import numpy as np
+import pytest
+
+import datagen
+from gpu_util import assert_same, oracle_rows, require_gpu, upload
+
+pytestmark = pytest.mark.gpu
+
+INV = pow(0x9E3779B1, -1, 1 << 32)      # the hash is key * 0x9E3779B1 mod 2^32
+
+
+def _keys_of_hashes(h):
+    return ((np.asarray(h, dtype=np.uint64) * INV) & 0xFFFFFFFF).astype(np.uint32).view(np.int32)
+
+
+def _workload(keys, n, seed, attr=None, groups=700, lf=0.5, fact_key=None, preds=True, agg="col"):
+    rng = np.random.default_rng([2607, 7632, 81, seed])
+    m = keys.size
+    if attr is None:
+        attr = rng.integers(0, groups, m, dtype=np.int32)
+    flag = rng.integers(0, 2, m, dtype=np.int32) if preds else np.ones(m, np.int32)
+    hit = keys[rng.integers(0, m, n)]
+    miss = rng.integers(-(1 << 31), 1 << 31, n).astype(np.int32)
+    fact = {"key": np.where(rng.random(n) < 0.8, hit, miss).astype(np.int32) if fact_key is None else fact_key,
+            "value": rng.integers(-(1 << 31), 1 << 31, n).astype(np.int32),
+            "other": rng.integers(-(1 << 31), 1 << 31, n).astype(np.int32)}
+    query = {"fact_preds": [{"col": "other", "op": "ge", "lo": -2_000_000_000, "hi": None}],
+             "joins": [{"fact_key": "key", "dim": "big", "preds": [{"col": "flag", "op": "eq", "lo": 1, "hi": None}],
+                        "payloads": ["attr"] if groups else [], "kind": "hash", "load_factor": lf}],
+             "group_by": [["big", "attr"]] if groups else [],
+             "agg": {"kind": agg, "a": "value", "b": None if agg == "col" else "other"}}
+    return datagen.Workload(f"seed {seed}", n, fact, {"big": {"key": keys, "flag": flag, "attr": attr}},
+                            {"big": "key"}, query)
+
+
+def _check(w, force=None, label="", short_scratch=0):
+    import torch
+    from paper_2607_07632_amd import sdb
+    require_gpu()
+    fact, dims = upload(w)
+    q = sdb.StarQuery(fact, sdb.build_dims(dims, w.dim_keys, w.query), w.query, {"slice": 1, **(force or {})})
+    plan = q.plan()
+    assert plan.slice_bits > 0
+    sums, counts = q.alloc_outputs()
+    scratch = torch.full((int(plan.run_scratch_bytes) - short_scratch,), 0xA5, dtype=torch.uint8, device="cuda")
+    q.run(sums, counts, scratch=scratch)
+    k, s, c, n, _ = q.finalize(sums, counts)
+    m = int(n.item())
+    got = sdb.QueryResult(k[:m, :q.n_keys].to(torch.int64).cpu().numpy().reshape(m, q.n_keys), s[:m].cpu().numpy(),
+                          c[:m].cpu().numpy())
+    assert_same(got.as_rows(), oracle_rows(w), f"{w.name} {force} {label}")
+
+
+@pytest.mark.parametrize("first", [0, (1 << 32) - (6000 << 10)])
+def test_a_slice_that_overfills_the_table(first):
+    """6,000 keys whose hashes lie in one slice (the first, or the last, whose
+    run of slots wraps around the table's end): more than the LDS table's
+    4,608 entries, in runs far past the slice's end."""
+    keys = _keys_of_hashes(first + (np.arange(6000, dtype=np.uint64) << 10))
+    for agg in ("col", "mul"):
+        _check(_workload(keys, 70_001, 1, lf=0.25, preds=False, agg=agg), label=agg)
+    _check(_workload(keys, 70_001, 2, lf=0.9), label="half pass")
+
+
+def test_slices_of_more_than_65536_slots():
+    keys = np.random.default_rng(5).choice(1 << 31, 2000, replace=False).astype(np.int32)
+    _check(_workload(keys, 30_003, 3, lf=0.0001))
+
+
+@pytest.mark.parametrize("groups,force", [(0, None), (1, None), (1024, None), (1025, None), (5000, None),
+                                          (5000, {"terminal": "part"}), (70_000, None), (1_100_000, None),
+                                          (5000, {"terminal": "global", "xcd": 1}), (300, {"terminal": "global", "xcd": 1}),
+                                          (300, {"terminal": "global", "xcd": -1})])
+def test_every_way_the_groups_leave(groups, force):
+    """Scalar and few groups (a block's LDS), more (records by range of 4,096
+    groups), more than 256 ranges (atomics), per-XCD copies."""
+    keys = np.random.default_rng(6).choice(1 << 31, 40_000, replace=False).astype(np.int32)
+    attr = np.random.default_rng(7).integers(0, max(groups, 1), keys.size, dtype=np.int32)
+    attr[:2] = 0, max(groups, 1) - 1
+    w = _workload(keys, 200_003, 8, attr=attr, groups=groups)
+    w.dims["big"]["flag"][:2] = 1
+    _check(w, force)
+
+
+def test_records_past_a_ranges_capacity():
+    """All rows but one in the first of 25 ranges of groups."""
+    keys = np.random.default_rng(9).choice(1 << 31, 60_000, replace=False).astype(np.int32)
+    attr = np.random.default_rng(10).integers(0, 4096, keys.size, dtype=np.int32)
+    attr[0] = 100_000
+    w = _workload(keys, 300_007, 11, attr=attr, preds=False)
+    _check(w)
+
+
+def test_a_hot_key_over_several_work_items():
+    """1.2M rows of one key (three work items of one partition), the int32
+    extremes among their values."""
+    keys = np.arange(-500, 500, dtype=np.int32)
+    n = 1_200_003
+    fk = np.full(n, 77, np.int32)
+    fk[::1000] = np.arange(fk[::1000].size, dtype=np.int32) - 600
+    w = _workload(keys, n, 12, fact_key=fk, preds=False)
+    w.fact["value"][:3] = -(1 << 31), (1 << 31) - 1, -(1 << 31)
+    _check(w)
+
+
+@pytest.mark.parametrize("n", [1, 5, 4099, 16_384, 131_075])
+def test_both_routes_at_chunk_edges(n):
+    """The LDS route, and with 256 bytes less of scratch the route through L2
+    (these plans' scratch is sized by the LDS route)."""
+    keys = np.random.default_rng(13).choice(1 << 31, 3000, replace=False).astype(np.int32)
+    w = _workload(keys, n, 14, groups=5000)
+    for agg in ("col", "sub"):
+        w.query["agg"] = {"kind": agg, "a": "value", "b": None if agg == "col" else "other"}
+        for short in (0, 256):
+            _check(w, {"terminal": "global", "xcd": -1}, f"{agg}, {short} bytes short", short)
