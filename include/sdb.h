@@ -361,7 +361,8 @@ enum { SDB_LDS_GLOBAL = 0, SDB_LDS_MAP = 1, SDB_LDS_BITS = 2, SDB_LDS_RANK = 3, 
  * (each dropped row saves a scatter write and a probe, each row costs one
  * L2-resident filter read). Where the passing rows of a 2,048th of the table
  * or more fit an LDS table (up to about 8.9M passing rows), the run takes
- * another route when its scratch holds it, as run_scratch_bytes always does:
+ * another route when its scratch holds it, as run_scratch_bytes does from 2^24
+ * fact rows on:
  * the rows are partitioned so finely (256 to 2,048 slices) that a block sums
  * each slice's rows by dimension row in LDS and only those totals go to their
  * groups; rows that cannot pass find no entry there, so it tests no pass

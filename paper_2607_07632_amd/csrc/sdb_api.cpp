@@ -1940,9 +1940,13 @@ SDB_API sdb_status sdb_plan_star_query(const sdb_query* q, void* scratch, int64_
             const double fp = d->filter_kind == SDB_FILTER_BLOOM ? bloom_false_positive(d->filter_bits, d->n_pass) : 0.0;
             plan->slice_prefilter = (q->force_prefilter == 1 || p + (1.0 - p) * fp <= kPrefilterMaxKept) ? 1 : 0;
         }
-        const int64_t copies = xcd ? (int64_t)copy_bytes : 0;
-        plan->run_scratch_bytes = std::max(plan->run_scratch_bytes + (int64_t)slice_layout(q, plan).total,
-                                           (int64_t)slice_agg_layout(q, plan).total + copies);
+        plan->run_scratch_bytes += (int64_t)slice_layout(q, plan).total;
+        // the LDS route's rows and records too, from the row count on that the
+        // planner takes slices by itself; a smaller (forced) plan takes that
+        // route when its caller's scratch happens to hold it
+        if (q->n_fact >= kSliceMinRows)
+            plan->run_scratch_bytes = std::max(plan->run_scratch_bytes, (int64_t)slice_agg_layout(q, plan).total +
+                                                                            (xcd ? (int64_t)copy_bytes : 0));
     }
     return ok();
 }
@@ -2043,7 +2047,8 @@ SDB_API sdb_status sdb_run_star_query(const sdb_query* q, const sdb_plan* plan, 
 
     hipStream_t s = (hipStream_t)stream;
     // a sliced probe takes its LDS route where the table's slices fit LDS and
-    // the scratch holds that route's rows (a plan's run_scratch_bytes always does)
+    // the scratch holds that route's rows (as run_scratch_bytes of a plan for at
+    // least kSliceMinRows rows does)
     const SliceAggLayout AL = slice_agg_layout(q, plan);
     const uint64_t copy_bytes = plan->xcd_copies ? term_scratch : 0;
     const bool slice_agg = sliced && AL.bits > 0 && (uint64_t)scratch_bytes >= AL.total + copy_bytes;
@@ -2281,19 +2286,15 @@ SDB_API sdb_status sdb_run_star_query_noalloc(const sdb_query* q, const sdb_plan
                                               int64_t* counts, int64_t n_groups_capacity, void* stream) {
     sdb_status st = check_run(q, plan, sums, counts, n_groups_capacity);
     if (st != SDB_OK) return st;
-    const auto refuse = [&] {
+    if (plan->run_scratch_bytes < 0 || (uint64_t)plan->run_scratch_bytes > kNoallocScratchBytes)
         return fail(SDB_WORKSPACE_TOO_SMALL,
                     "the plan needs %lld bytes of run scratch; the fixed scratch of the allocation-free run holds "
                     "%llu (plan with the global terminal, no per-XCD copies and no table slices)",
                     (long long)plan->run_scratch_bytes, (unsigned long long)kNoallocScratchBytes);
-    };
-    // (a sliced probe's run_scratch_bytes may count its LDS route, which it can do without)
-    const bool beyond = plan->run_scratch_bytes < 0 || (uint64_t)plan->run_scratch_bytes > kNoallocScratchBytes;
-    if (beyond && (plan->run_scratch_bytes < 0 || plan->slice_bits == 0)) return refuse();
     void* fixed = nullptr;
     SDB_HIP(noalloc_scratch(&fixed), "fixed run scratch address");
-    st = sdb_run_star_query(q, plan, sums, counts, n_groups_capacity, fixed, (int64_t)kNoallocScratchBytes, stream);
-    return beyond && st == SDB_WORKSPACE_TOO_SMALL ? refuse() : st;
+    return sdb_run_star_query(q, plan, sums, counts, n_groups_capacity, fixed, (int64_t)kNoallocScratchBytes,
+                              stream);
 }
 
 SDB_API sdb_status sdb_baseline_scratch_bytes(int64_t n_fact, int64_t* bytes) {

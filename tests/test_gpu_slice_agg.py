@@ -39,7 +39,7 @@ def _workload(keys, n, seed, attr=None, groups=700, lf=0.5, fact_key=None, preds
                             {"big": "key"}, query)
 
 
-def _check(w, force=None, label="", short_scratch=0):
+def _check(w, force=None, label="", through_l2=False):
     import torch
     from paper_2607_07632_amd import sdb
     require_gpu()
@@ -48,7 +48,9 @@ def _check(w, force=None, label="", short_scratch=0):
     plan = q.plan()
     assert plan.slice_bits > 0
     sums, counts = q.alloc_outputs()
-    scratch = torch.full((int(plan.run_scratch_bytes) - short_scratch,), 0xA5, dtype=torch.uint8, device="cuda")
+    # (a plan for so few rows does not count the LDS route's scratch)
+    need = int(plan.run_scratch_bytes) + (0 if through_l2 else 128 << 20)
+    scratch = torch.full((need,), 0xA5, dtype=torch.uint8, device="cuda")
     q.run(sums, counts, scratch=scratch)
     k, s, c, n, _ = q.finalize(sums, counts)
     m = int(n.item())
@@ -111,11 +113,11 @@ def test_a_hot_key_over_several_work_items():
 
 @pytest.mark.parametrize("n", [1, 5, 4099, 16_384, 131_075])
 def test_both_routes_at_chunk_edges(n):
-    """The LDS route, and with 256 bytes less of scratch the route through L2
-    (these plans' scratch is sized by the LDS route)."""
+    """The LDS route, and the route through L2 in the plan's own scratch, which
+    is too small for the other's records."""
     keys = np.random.default_rng(13).choice(1 << 31, 3000, replace=False).astype(np.int32)
     w = _workload(keys, n, 14, groups=5000)
     for agg in ("col", "sub"):
         w.query["agg"] = {"kind": agg, "a": "value", "b": None if agg == "col" else "other"}
-        for short in (0, 256):
-            _check(w, {"terminal": "global", "xcd": -1}, f"{agg}, {short} bytes short", short)
+        for l2 in (False, True):
+            _check(w, {"terminal": "global", "xcd": -1}, f"{agg}, {'L2' if l2 else 'LDS'}", l2)
