@@ -394,7 +394,9 @@ typedef struct sdb_plan {
     double est_cost;                      /* cost model value of the chosen order */
     int32_t terminal;
     int32_t ipt;
-    int32_t vector;                       /* 1: 4-row items with 128-bit loads */
+    int32_t vector;                       /* 1: 4-row items with 16-byte aligned 128-bit loads; 0: 1-row
+                                             items where force_vector = -1 or a hash table is
+                                             probed, else 4-row items with unaligned loads */
     int32_t eager;                        /* columns loaded together when items start (first in order of use) */
     int32_t block;
     int32_t grid;                         /* 0: chosen at launch */

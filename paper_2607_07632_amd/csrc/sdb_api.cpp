@@ -388,6 +388,26 @@ sdb_status check_query(const sdb_query* q) {
     return SDB_OK;
 }
 
+// Whether a stage probes a hash table.
+bool probes_hash(const sdb_query* q, const sdb_plan* plan) {
+    for (int s = 0; s < plan->n_stages; ++s)
+        if (plan->stage_kind[s] == 1 && !plan->stage_range[s] &&
+            q->joins[plan->stage_index[s]].dim->kind != SDB_TABLE_DENSE)
+            return true;
+    return false;
+}
+
+// Whether the fused kernel runs 4-row items: on 16-byte aligned columns
+// (plan->vector), and on others unless 1-row items are forced. A 128-bit load
+// needs 4-byte alignment only; off 16 bytes a wave's loads touch one line
+// more. Measured against 1-row items: the join of 20M rows 116 -> 77 us, a
+// scan of 80M 306 -> 195, stars of 50M 342 -> 244 (three dimensions) and 261
+// -> 166 (four); but a probe of a hash table larger than L2 1,006 -> 1,022, so
+// plans that probe one keep 1-row items.
+bool wide_items(const sdb_query* q, const sdb_plan* plan) {
+    return plan->vector || (q->force_vector != -1 && plan->slice_bits == 0 && !probes_hash(q, plan));
+}
+
 // Whether the plan may run the fused kernel's instance with the stage loop
 // written out kUnrollStages times. The instance exists for 4-row items, two
 // items per lane, blocks of kMaxBlock or kBigBlock and no eager loads. Unrolled, each
@@ -397,14 +417,16 @@ sdb_status check_query(const sdb_query* q) {
 // 0.173 -> 0.157 ms) but not a hash probe (c5 3% slower; c4, with one item
 // per lane, 40%), so hash probes keep the loop.
 bool unroll_allowed(const sdb_query* q, const sdb_plan* plan) {
-    if (!plan->vector || plan->ipt != 2 || plan->eager != 0 || (plan->block != kMaxBlock && plan->block != kBigBlock))
-        return false;
-    if (plan->n_stages > kUnrollStages || plan->slice_bits != 0) return false;
-    for (int s = 0; s < plan->n_stages; ++s)
-        if (plan->stage_kind[s] == 1 && !plan->stage_range[s] &&
-            q->joins[plan->stage_index[s]].dim->kind != SDB_TABLE_DENSE)
-            return false;
-    return true;
+    if (!wide_items(q, plan) || plan->ipt != 2 || plan->eager != 0) return false;
+    if (plan->vector && plan->block != kMaxBlock && plan->block != kBigBlock) return false;
+    return plan->n_stages <= kUnrollStages && plan->slice_bits == 0 && !probes_hash(q, plan);
+}
+
+// The instance a run takes: the plan's choice, and for 4-row items on
+// unaligned columns (plan->vector and so plan->unroll 0) the same rule.
+int run_unroll(const sdb_query* q, const sdb_plan* plan) {
+    if (plan->vector) return plan->unroll;
+    return q->force_unroll != -1 && unroll_allowed(q, plan) ? 1 : 0;
 }
 
 // Group radices and strides: key k's code ranges over its payload radix;
@@ -1119,7 +1141,8 @@ uint32_t launch_lds_bytes(const sdb_query* q, const sdb_plan* plan) {
 constexpr uint32_t kLdsUsable = 152u * 1024u;
 
 sdb_status choose_grid(const sdb_query* q, const sdb_plan* plan, int* grid_out) {
-    const int64_t rows_per_item = plan->vector ? 4 : 1;
+    const int wide = wide_items(q, plan) ? 1 : 0;
+    const int64_t rows_per_item = wide ? 4 : 1;
     const int64_t n_items = q->n_fact / rows_per_item;
     const int64_t tile = (int64_t)plan->block * plan->ipt;
     int64_t tiles = (n_items + tile - 1) / tile;
@@ -1131,7 +1154,7 @@ sdb_status choose_grid(const sdb_query* q, const sdb_plan* plan, int* grid_out) 
     DeviceInfo di;
     sdb_status st = device_info(&di);
     if (st != SDB_OK) return st;
-    int per_cu = fused_blocks_per_cu(plan->vector, plan->ipt, plan->terminal, plan->eager, plan->block, plan->unroll,
+    int per_cu = fused_blocks_per_cu(wide, plan->ipt, plan->terminal, plan->eager, plan->block, run_unroll(q, plan),
                                      (size_t)launch_lds_bytes(q, plan));
     if (per_cu <= 0) return fail(SDB_HIP_ERROR, "occupancy query failed for the fused kernel");
     // The occupancy query counts LDS as if all 160 KB were available in fine
@@ -1193,7 +1216,7 @@ int place_window(const sdb_query* q, sdb_plan* plan, const Sample& smp, const in
     int order[SDB_MAX_STAGES];
     for (int i = 0; i < plan->n_stages; ++i) order[i] = i;
     const uint64_t used = lds_layout(q, plan, nullptr) + ring_lds_bytes(q, plan);
-    int per_cu = fused_blocks_per_cu(plan->vector, plan->ipt, plan->terminal, plan->eager, plan->block,
+    int per_cu = fused_blocks_per_cu(wide_items(q, plan), plan->ipt, plan->terminal, plan->eager, plan->block,
                                      unroll_allowed(q, plan) && q->force_unroll != -1 ? 1 : 0, (size_t)used);
     if (per_cu < 1) per_cu = 1;
     const uint64_t per_block = (uint64_t)kLdsUsable / (uint64_t)per_cu / 2048u * 2048u;
@@ -1875,7 +1898,7 @@ SDB_API sdb_status sdb_plan_star_query(const sdb_query* q, void* scratch, int64_
     }
     plan->lds_bytes = (int32_t)lds_layout(q, plan, nullptr);
     const uint64_t stage_bytes = stage_scratch_bytes(q, plan);
-    plan->unroll = (q->force_unroll != -1 && slice_j < 0 && unroll_allowed(q, plan)) ? 1 : 0;
+    plan->unroll = (q->force_unroll != -1 && slice_j < 0 && plan->vector && unroll_allowed(q, plan)) ? 1 : 0;
 
     // per-XCD private group tables for the global terminal when enough rows survive
     const uint64_t copy_bytes = (uint64_t)kXcdCopies * plan->n_groups * 16;
@@ -2014,7 +2037,7 @@ SDB_API sdb_status sdb_run_star_query(const sdb_query* q, const sdb_plan* plan, 
          q->joins[plan->stage_index[plan->slice_stage]].dim->filter_kind == SDB_FILTER_NONE))
         return fail(SDB_INVALID_ARG, "slice_prefilter %d needs a sliced probe into a table with a pass filter",
                     plan->slice_prefilter);
-    if (plan->unroll != 0 && (plan->unroll != 1 || !unroll_allowed(q, plan)))
+    if (plan->unroll != 0 && (plan->unroll != 1 || !plan->vector || !unroll_allowed(q, plan)))
         return fail(SDB_INVALID_ARG, "bad plan unroll %d (needs at most %d stages, 4-row items, ipt 2, blocks of "
                     "%d or %d, no eager loads, no hash probe and no table slices)", plan->unroll, kUnrollStages,
                     kMaxBlock, kBigBlock);
@@ -2268,7 +2291,7 @@ SDB_API sdb_status sdb_run_star_query(const sdb_query* q, const sdb_plan* plan, 
                 }
                 pg.region_base = (uint32_t)((uint64_t)g * (uint64_t)grid);
             }
-            SDB_HIP(launch_fused(pg, plan->vector, plan->ipt, plan->terminal, plan->eager, plan->unroll, grid,
+            SDB_HIP(launch_fused(pg, wide_items(q, plan), plan->ipt, plan->terminal, plan->eager, run_unroll(q, plan), grid,
                                  plan->block, lds_bytes, s),
                     "fused kernel launch");
         }

@@ -10,6 +10,7 @@
 namespace sdb {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef v4i __attribute__((aligned(4))) v4i_a4;       // four rows of a column that need not be 16-byte aligned
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
 typedef u64x2 __attribute__((aligned(8))) u64x2_a8;   // two adjacent 8-byte slots
@@ -42,7 +43,7 @@ __device__ __forceinline__ int32_t wave_max_i32(int32_t v) {
 template <int W>
 __device__ __forceinline__ void load_item(const int32_t* col, int64_t item, int32_t (&x)[W]) {
     if constexpr (W == 4) {
-        v4i v = __builtin_nontemporal_load(reinterpret_cast<const v4i*>(col) + item);
+        v4i v = __builtin_nontemporal_load(reinterpret_cast<const v4i_a4*>(col) + item);
         x[0] = v.x;
         x[1] = v.y;
         x[2] = v.z;

@@ -841,7 +841,7 @@ hipError_t launch_xcd_merge(const unsigned long long* xtab, int copies, uint64_t
 static const void* pick_fused(int vector, int ipt, int terminal, int eager, int block, int unroll) {
     if (unroll) {
         if (!vector || ipt != 2 || eager > 0) return nullptr;
-        if (block == kMaxBlock) return pick_fused_unrolled(terminal);
+        if (block <= kMaxBlock) return pick_fused_unrolled(terminal);
         if (block == kBigBlock) return pick_fused_unrolled_big(terminal);
         return nullptr;
     }
