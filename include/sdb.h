@@ -468,7 +468,10 @@ SDB_API sdb_status sdb_struct_sizes(int64_t* sizes, int32_t n);
  * dense_budget_bytes plus 512 bytes of alignment when that is larger, and/or
  * a HASH table of next_pow2(n_rows / load_factor) 8-byte slots, padded to
  * 256 bytes, and its pass filter of min(max(next_pow2(n_rows), 256),
- * SDB_MAX_FILTER_BYTES) bytes). */
+ * SDB_MAX_FILTER_BYTES) bytes). A workspace with 9 bytes a row and 4 MiB more
+ * lets a hash table of 2^19 rows or more (at most 2^25 slots) be built slice
+ * by slice: its rows partitioned there by table slice, each slice built in
+ * LDS and written whole, instead of inserts all over the table. */
 SDB_API sdb_status sdb_dim_required_bytes(const sdb_dim_desc* desc, int64_t* bytes);
 
 /* Builds the lookup table for `desc` into `workspace` (device, 256-byte
@@ -477,7 +480,8 @@ SDB_API sdb_status sdb_dim_required_bytes(const sdb_dim_desc* desc, int64_t* byt
  * count, payload ranges), then the direct-mapped map (Section 3.3: one code
  * per key, the sentinel for a filtered row, all ones for an absent key; 1, 2
  * or 4 bytes by payload domain) and its pass bitmap, or the open-addressing
- * table (64-bit compare-and-swap inserts) and its pass filter (a bitmap over
+ * table (64-bit compare-and-swap inserts, in LDS slice by slice where the
+ * workspace has room for it) and its pass filter (a bitmap over
  * the key range when that fits the filter's bytes, set through one byte per
  * key in the slot region before the slots are filled; else the Bloom filter,
  * set with atomics by the inserts).

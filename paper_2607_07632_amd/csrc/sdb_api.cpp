@@ -284,6 +284,37 @@ uint64_t required_bytes(const sdb_dim_desc* d) {
     return kStatsBytes + table;
 }
 
+// The sliced build of a hash table of 2^hash_bits slots in the workspace past
+// what sdb_dim_required_bytes counts: true, with the parameters filled, where
+// the table is of its sizes and that room suffices.
+bool hash_slices(const sdb_dim_desc* desc, const BuildParams& bp, int hash_bits, uint8_t* workspace,
+                 uint64_t workspace_bytes, HashSliceParams* hp) {
+    const uint64_t n = (uint64_t)desc->n_rows;
+    if (desc->n_rows < kHashSliceMinRows) return false;
+    const int bits = std::max(hash_bits - kHashSliceSlotBits, std::min(8, hash_bits));
+    if (bits > kSliceMaxBits) return false;
+    const uint64_t P = 1ull << bits;
+    uint64_t off = align_up(required_bytes(desc), 256);
+    auto take = [&](uint64_t bytes) {
+        const uint64_t at = off;
+        off += align_up(bytes, 256);
+        return workspace + at;
+    };
+    std::memset(hp, 0, sizeof *hp);
+    hp->bp = bp;
+    hp->bits = bits;
+    hp->spill_cap = (uint32_t)(n / 16);
+    hp->rows_per_block = (int64_t)((n + kHashSliceGrid - 1) / kHashSliceGrid);
+    hp->hist = (uint32_t*)take(P * kHashSliceGrid * 4);
+    hp->part_count = (uint32_t*)take(P * 4);
+    hp->part_start = (uint32_t*)take((P + 1) * 4);
+    hp->chunk_start = (uint32_t*)take((P + 1) * 4);
+    hp->spill_n = (uint32_t*)take(4);
+    hp->rec = (unsigned long long*)take(n * 8);
+    hp->spill = (unsigned long long*)take((uint64_t)hp->spill_cap * 8);
+    return off <= workspace_bytes;
+}
+
 BuildParams build_params(const sdb_dim_desc* d, DimStats* stats) {
     BuildParams bp;
     std::memset(&bp, 0, sizeof bp);
@@ -1427,6 +1458,7 @@ SDB_API sdb_status sdb_build_dims(int32_t n_dims, const sdb_dim_desc* descs, voi
 
     // pass 2 for every table: layout from the statistics, then the map or hash table
     int kinds[SDB_MAX_JOINS];
+    HashSliceParams slices[SDB_MAX_JOINS];
     for (int d = 0; d < n_dims; ++d) {
         const sdb_dim_desc* desc = &descs[d];
         sdb_dim* out = &outs[d];
@@ -1527,18 +1559,41 @@ SDB_API sdb_status sdb_build_dims(int32_t n_dims, const sdb_dim_desc* descs, voi
             // there; the slots are filled afterwards, the filter by the packing
             bp[d].filt_via_bytes = bitmap && align_up(range, 32) <= slot_bytes ? 1 : 0;
             bp[d].fill_words = (slot_bytes + (bp[d].filt_via_bytes ? 0 : fbytes)) / 4;
+            if (hash_slices(desc, bp[d], bits, (uint8_t*)workspaces[d], (uint64_t)workspace_bytes[d], &slices[d])) {
+                bp[d].sliced = 1;
+                bp[d].fill_words = 0;   // every slot is written by its slice
+            }
         }
     }
 
     SDB_HIP(launch_build_tables(bb, s), "table build launch");
+    for (int d = 0; d < n_dims; ++d)
+        if (bp[d].sliced) SDB_HIP(launch_hash_slices(slices[d], s), "sliced build launch");
 
-    // duplicate-key checks of every table, with one synchronization
-    if (bb.host_stats)
-        SDB_HIP(launch_export_stats(bb, s), "flag export launch");
-    else
-        for (int d = 0; d < n_dims; ++d)
-            SDB_HIP(hipMemcpyAsync(&hs[d], workspaces[d], sizeof(DimStats), hipMemcpyDeviceToHost, s), "flag copy");
-    if (n_dims > 0) SDB_HIP(hipStreamSynchronize(s), "build sync");
+    // duplicate-key checks of every table, with one synchronization (and
+    // another after tables whose keys hash too unevenly for slices have been
+    // built again with inserts)
+    for (;;) {
+        if (bb.host_stats)
+            SDB_HIP(launch_export_stats(bb, s), "flag export launch");
+        else
+            for (int d = 0; d < n_dims; ++d)
+                SDB_HIP(hipMemcpyAsync(&hs[d], workspaces[d], sizeof(DimStats), hipMemcpyDeviceToHost, s), "flag copy");
+        if (n_dims > 0) SDB_HIP(hipStreamSynchronize(s), "build sync");
+        bool again = false;
+        for (int d = 0; d < n_dims; ++d) {
+            if (!bp[d].sliced || !(hs[d].dup & kHashSliceRetry)) continue;
+            again = true;
+            bp[d].sliced = 0;
+            BuildBatch one;
+            std::memset(&one, 0, sizeof one);
+            one.n = 1;
+            one.bp[0] = slices[d].bp;   // as it was before the slices: filled, inserted
+            SDB_HIP(launch_fill_u32(&bp[d].stats->dup, 1, 0u, s), "flag fill");
+            SDB_HIP(launch_build_tables(one, s), "table build launch");
+        }
+        if (!again) break;
+    }
     for (int d = 0; d < n_dims; ++d) {
         const DimStats& fin = hs[d];
         if (fin.dup & 1u) return fail(SDB_DUP_KEY, "dimension %d: key column holds a duplicate key", d);

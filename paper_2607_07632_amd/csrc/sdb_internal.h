@@ -249,7 +249,6 @@ struct BuildParams {
     DimStats* stats;
     DimStats* stats_part;      // stats_blocks partial statistics (in the table region)
     int32_t stats_blocks;
-    int32_t pad3_;
     void* map;                 // dense map or hash table
     uint32_t* pass_bits;       // dense pass bitmap
     int32_t width;
@@ -259,7 +258,8 @@ struct BuildParams {
     uint32_t missing;          // dense: code of a key no row holds (all ones)
     uint32_t hmask;
     int32_t hshift;
-    int32_t dense;             // 1: dense map (scatter + bitmap), 0: hash table (inserts)
+    int32_t dense;             // 1: dense map (scatter + bitmap), 0: hash table
+    int32_t sliced;            // hash: built slice by slice (launch_hash_slices), not by inserts
     uint32_t fill_value;       // the table's initial word value (all ones dense, 0 hash)
     uint64_t fill_words;       // 32-bit words of the table to fill before the scatter / inserts
                                // (a hash table's pass filter follows its slots and is filled too)
@@ -270,6 +270,31 @@ struct BuildParams {
                                // region before the slots are filled (no atomics); 0: the
                                // inserts set its bits with atomics
 };
+
+// Sliced build of a hash table (hash_slice_kernel): rows partitioned by table
+// slice, each slice built in LDS. Tables of kHashSliceMinRows rows or more
+// (a step with a table of 530K rows takes 157 us by inserts and 155 by slices,
+// of 1M rows 238 and 181) and at most 2^25 slots, where the workspace has room
+// for the records.
+constexpr int kHashSliceSlotBits = 14;          // at most 2^14 slots a slice (128 KB of LDS)
+constexpr int64_t kHashSliceMinRows = 1ll << 19;
+constexpr int kHashSliceGrid = 256;             // blocks of its count and scatter passes
+constexpr uint32_t kHashSliceRetry = 8u;        // DimStats.dup: too uneven for slices, build with inserts
+
+struct HashSliceParams {
+    BuildParams bp;
+    int32_t bits;              // 2^bits slices
+    uint32_t spill_cap;
+    int64_t rows_per_block;
+    uint32_t* hist;            // as SliceParams
+    uint32_t* part_count;
+    uint32_t* part_start;
+    uint32_t* chunk_start;
+    uint32_t* spill_n;         // rows whose slots lie past their slice's end
+    unsigned long long* rec;   // slot values, slice after slice
+    unsigned long long* spill; // spill_cap of them
+};
+hipError_t launch_hash_slices(const HashSliceParams& hp, hipStream_t s);
 
 // Every table of one sdb_build_dims call; kernels take table blockIdx.y.
 struct BuildBatch {

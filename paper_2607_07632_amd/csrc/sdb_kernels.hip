@@ -466,37 +466,45 @@ __device__ __forceinline__ bool filter_slot(int32_t kind, uint64_t nbits, int32_
     return true;
 }
 
-// Open addressing, linear probing, 8-byte slots {key, code + 1 | 0xFFFFFFFF};
-// a passing row's key also goes into the table's pass filter.
+// The slot value of dimension row i: {key, code + 1 | 0xFFFFFFFF}.
+__device__ __forceinline__ unsigned long long hash_slot_value(const BuildParams& bp, int64_t i) {
+    const uint32_t enc = dim_row_passes(bp, i) ? dim_row_code(bp, i) + 1u : 0xFFFFFFFFu;
+    return ((unsigned long long)enc << 32) | (uint32_t)bp.key[i];
+}
+
+// A passing row's key goes into the table's pass filter.
+__device__ __forceinline__ void hash_filter_key(const BuildParams& bp, unsigned long long slot) {
+    uint32_t fw, fm;
+    if (bp.filt && !bp.filt_via_bytes && (uint32_t)(slot >> 32) != 0xFFFFFFFFu &&
+        filter_slot(bp.filt_kind, bp.filt_bits, bp.kmin, (int32_t)(uint32_t)slot, fw, fm))
+        atomicOr(&bp.filt[fw], fm);
+}
+
+// Open addressing, linear probing, 8-byte slots.
+__device__ __forceinline__ void hash_place(const BuildParams& bp, unsigned long long slot) {
+    unsigned long long* tab = static_cast<unsigned long long*>(bp.map);
+    const uint32_t k = (uint32_t)slot;
+    uint32_t h = (k * 0x9E3779B1u) >> bp.hshift & bp.hmask;
+    for (uint64_t it = 0; it < bp.nslots; ++it) {
+        const unsigned long long old = atomicCAS(&tab[h], 0ull, slot);
+        if (old == 0ull) return;
+        if ((uint32_t)old == k) {
+            atomicOr(&bp.stats->dup, 1u);
+            return;
+        }
+        h = (h + 1u) & bp.hmask;
+    }
+    atomicOr(&bp.stats->dup, 2u);
+}
+
 __global__ void __launch_bounds__(256) hash_insert_kernel(BuildBatch kernel_args) {
     SDB_BATCH_TABLE;
-    if (bp.dense) return;
-    unsigned long long* tab = static_cast<unsigned long long*>(bp.map);
+    if (bp.dense || bp.sliced) return;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < bp.n; i += stride) {
-        const int32_t k = bp.key[i];
-        const uint32_t enc = dim_row_passes(bp, i) ? dim_row_code(bp, i) + 1u : 0xFFFFFFFFu;
-        const unsigned long long slot = ((unsigned long long)enc << 32) | (uint32_t)k;
-        uint32_t fw, fm;
-        if (bp.filt && !bp.filt_via_bytes && enc != 0xFFFFFFFFu &&
-            filter_slot(bp.filt_kind, bp.filt_bits, bp.kmin, k, fw, fm))
-            atomicOr(&bp.filt[fw], fm);
-        uint32_t h = ((uint32_t)k * 0x9E3779B1u) >> bp.hshift & bp.hmask;
-        bool placed = false;
-        for (uint64_t it = 0; it < bp.nslots; ++it) {
-            const unsigned long long old = atomicCAS(&tab[h], 0ull, slot);
-            if (old == 0ull) {
-                placed = true;
-                break;
-            }
-            if ((int32_t)(uint32_t)old == k) {
-                atomicOr(&bp.stats->dup, 1u);
-                placed = true;
-                break;
-            }
-            h = (h + 1u) & bp.hmask;
-        }
-        if (!placed) atomicOr(&bp.stats->dup, 2u);
+        const unsigned long long slot = hash_slot_value(bp, i);
+        hash_filter_key(bp, slot);
+        hash_place(bp, slot);
     }
 }
 
@@ -595,7 +603,7 @@ hipError_t launch_build_tables(const BuildBatch& bb, hipStream_t s) {
         if (bp.dense) {
             n_dense = std::max<int64_t>(n_dense, bp.n);
             n_words32 = std::max<uint64_t>(n_words32, (bp.nslots + 31) / 32);
-        } else {
+        } else if (!bp.sliced) {
             n_hash = std::max<int64_t>(n_hash, bp.n);
         }
         if (bp.filt_via_bytes) {
@@ -1734,8 +1742,10 @@ __device__ __forceinline__ void slice_write_window(const SliceParams& sp, const 
 // a chunk's rows (4 * G a thread) stay in registers and only WINDOW of them
 // at a time pass through LDS in partition order. Bound by the runs' partial
 // lines. The next chunk's loads are issued before the last window is written.
-template <int G, bool TWO>
-__global__ void __launch_bounds__(kSliceBlock) slice_scatter_rec_kernel(SliceParams sp) {
+// `load(at, n, k, v, v2)` reads a thread's rows of the n at row `at` and
+// returns which of them are there.
+template <int G, bool TWO, class Load>
+__device__ __forceinline__ void slice_scatter_rows(const SliceParams& sp, const Load& load_rows) {
     constexpr int RPT = 4 * G, CHUNK = RPT * kSliceBlock;
     constexpr uint32_t WINDOW = TWO ? 8192u : 16384u;
     static_assert(CHUNK <= 65536, "16-bit places in a chunk");
@@ -1754,16 +1764,9 @@ __global__ void __launch_bounds__(kSliceBlock) slice_scatter_rec_kernel(SlicePar
     __syncthreads();
     const int64_t r0 = (int64_t)blockIdx.x * sp.rows_per_block;
     const int64_t r1 = min(sp.n, r0 + sp.rows_per_block);
-    const int32_t* val = sp.cols[sp.val_col];
-    const int32_t* val2 = sp.cols[TWO ? sp.val2_col : sp.val_col];
     int32_t k[RPT], v[RPT], v2[TWO ? RPT : 4];
     uint32_t live = 0u;
-    const auto load = [&](int64_t at) {
-        const uint32_t n = (uint32_t)min(r1 - at, (int64_t)CHUNK);
-        live = slice_load_live<G>(sp, at, n, k);
-        slice_load_values<G>(val + at, n, live, v);
-        if constexpr (TWO) slice_load_values<G>(val2 + at, n, live, v2);
-    };
+    const auto load = [&](int64_t at) { live = load_rows(at, (uint32_t)min(r1 - at, (int64_t)CHUNK), k, v, v2); };
     if (r0 < r1) load(r0);
     for (int64_t c0 = r0; c0 < r1; c0 += CHUNK) {
         // each row's rank in its partition, then its place in partition order, two to a register
@@ -1813,6 +1816,16 @@ __global__ void __launch_bounds__(kSliceBlock) slice_scatter_rec_kernel(SlicePar
         }
         __syncthreads();
     }
+}
+
+template <int G, bool TWO>
+__global__ void __launch_bounds__(kSliceBlock) slice_scatter_rec_kernel(SliceParams sp) {
+    slice_scatter_rows<G, TWO>(sp, [&](int64_t at, uint32_t n, int32_t (&k)[4 * G], int32_t (&v)[4 * G], auto& v2) {
+        const uint32_t live = slice_load_live<G>(sp, at, n, k);
+        slice_load_values<G>(sp.cols[sp.val_col] + at, n, live, v);
+        if constexpr (TWO) slice_load_values<G>(sp.cols[sp.val2_col] + at, n, live, v2);
+        return live;
+    });
 }
 
 size_t slice_scatter_rec_lds_bytes(uint32_t n_parts, bool two) {
@@ -2309,6 +2322,167 @@ hipError_t launch_slice_agg(const SliceAggParams& ap, int grid, hipStream_t s) {
     const uint32_t chunks = (ap.emit_cap + kSliceEmitChunk - 1u) / kSliceEmitChunk;
     hipLaunchKernelGGL(slice_merge_kernel, dim3(chunks, ap.emit_ranges), dim3(1024),
                        (size_t)16u << kSliceEmitShift, s, ap);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// sliced build of a hash table
+// ---------------------------------------------------------------------------
+
+// Compare-and-swap inserts all over a table larger than the caches run at
+// about 9G rows/s (8.4M rows into 2^24 slots: 978 us, and 20 us to fill them;
+// this build 275 us, 183 of them the slices, whose Bloom filter bits are
+// atomics bound for the memory side). Here the rows' slot values are first
+// partitioned by table slice (the probe's own passes), each slice is built in
+// LDS and written whole, and the few rows whose linear probing leaves their
+// slice are inserted last; no slot is filled before.
+__global__ void __launch_bounds__(kSliceBlock) hash_count_kernel(HashSliceParams hp) {
+    __shared__ uint32_t lh[1 << kSliceMaxBits];
+    const uint32_t P = 1u << hp.bits;
+    for (uint32_t q = threadIdx.x; q < P; q += kSliceBlock) lh[q] = 0u;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *hp.spill_n = 0u;
+    __syncthreads();
+    const int64_t r0 = (int64_t)blockIdx.x * hp.rows_per_block;
+    const int64_t r1 = min(hp.bp.n, r0 + hp.rows_per_block);
+    constexpr int U = 16;
+    for (int64_t i0 = r0 + threadIdx.x; i0 < r1; i0 += U * kSliceBlock) {
+        int32_t k[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) k[u] = i0 + u * kSliceBlock < r1 ? hp.bp.key[i0 + u * kSliceBlock] : 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i0 + u * kSliceBlock < r1) atomicAdd(&lh[slice_of(k[u], hp.bits)], 1u);
+    }
+    __syncthreads();
+    for (uint32_t q = threadIdx.x; q < P; q += kSliceBlock) hp.hist[(uint64_t)q * gridDim.x + blockIdx.x] = lh[q];
+}
+
+__global__ void __launch_bounds__(kSliceBlock) hash_scatter_kernel(HashSliceParams hp) {
+    SliceParams sp;
+    sp.n = hp.bp.n;
+    sp.rows_per_block = hp.rows_per_block;
+    sp.bits = hp.bits;
+    sp.hist = hp.hist;
+    sp.part_start = hp.part_start;
+    sp.out_rec = hp.rec;
+    constexpr int G = 4;
+    slice_scatter_rows<G, false>(sp, [&](int64_t at, uint32_t n, int32_t (&k)[4 * G], int32_t (&v)[4 * G], auto&) {
+        uint32_t live = 0u, pass;
+        int32_t x[4 * G];
+        const BuildParams& bp = hp.bp;
+        const auto column = [&](const int32_t* col, int32_t (&to)[4 * G], uint32_t which) {
+#pragma unroll
+            for (int u = 0; u < 4 * G; ++u)
+                to[u] = (which >> u) & 1u ? col[at + (uint32_t)u * kSliceBlock + threadIdx.x] : 0;
+        };
+#pragma unroll
+        for (int u = 0; u < 4 * G; ++u) live |= ((uint32_t)u * kSliceBlock + threadIdx.x < n ? 1u : 0u) << u;
+        column(bp.key, k, live);
+        pass = live;
+        for (int q = 0; q < bp.n_preds; ++q) {
+            column(bp.cols[bp.pred_col[q]], x, live);
+#pragma unroll
+            for (int u = 0; u < 4 * G; ++u)
+                if (!range_pass(bp.pred[q], x[u])) pass &= ~(1u << u);
+        }
+#pragma unroll
+        for (int u = 0; u < 4 * G; ++u) v[u] = 1;   // code + 1
+        for (int p = 0; p < bp.n_payloads; ++p) {
+            column(bp.cols[bp.payload_col[p]], x, pass);
+#pragma unroll
+            for (int u = 0; u < 4 * G; ++u)
+                v[u] = (int32_t)((uint32_t)v[u] + ((uint32_t)x[u] - (uint32_t)bp.pmin[p]) * bp.pdiv[p]);
+        }
+#pragma unroll
+        for (int u = 0; u < 4 * G; ++u)
+            if (!((pass >> u) & 1u)) v[u] = -1;
+        return live;
+    });
+}
+
+// One block per slice.
+__global__ void __launch_bounds__(1024) hash_slice_kernel(HashSliceParams hp) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    unsigned long long* slots = reinterpret_cast<unsigned long long*>(smem);
+    const BuildParams& bp = hp.bp;
+    const uint32_t q = blockIdx.x, per = (uint32_t)(bp.nslots >> hp.bits);
+    const uint32_t r0 = hp.part_start[q], n = hp.part_start[q + 1] - r0;
+    if (n > per) {   // cannot fit: the host builds this table with inserts
+        if (threadIdx.x == 0) atomicOr(&bp.stats->dup, kHashSliceRetry);
+        return;
+    }
+    for (uint32_t i = threadIdx.x; i < per; i += 1024u) slots[i] = 0ull;
+    __syncthreads();
+    constexpr int U = 8;
+    for (uint32_t i0 = threadIdx.x; i0 < n; i0 += U * 1024u) {
+        unsigned long long rec[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            rec[u] = i0 + u * 1024u < n ? __builtin_nontemporal_load(hp.rec + r0 + (i0 + u * 1024u)) : 0ull;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (i0 + u * 1024u >= n) continue;
+            hash_filter_key(bp, rec[u]);
+            const uint32_t k = (uint32_t)rec[u];
+            uint32_t h = ((k * 0x9E3779B1u) >> bp.hshift) & (per - 1u);
+            for (;;) {
+                const unsigned long long old = atomicCAS(&slots[h], 0ull, rec[u]);
+                if (old == 0ull) break;
+                if ((uint32_t)old == k) {
+                    atomicOr(&bp.stats->dup, 1u);
+                    break;
+                }
+                if (++h == per) {
+                    const uint32_t at = atomicAdd(hp.spill_n, 1u);
+                    if (at < hp.spill_cap) hp.spill[at] = rec[u];
+                    else atomicOr(&bp.stats->dup, kHashSliceRetry);
+                    break;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    unsigned long long* tab = static_cast<unsigned long long*>(bp.map) + (uint64_t)q * per;
+    for (uint32_t i = threadIdx.x; i < per; i += 1024u) tab[i] = slots[i];
+}
+
+// The rows past their slices' ends, once every slice is written.
+__global__ void __launch_bounds__(256) hash_spill_kernel(HashSliceParams hp) {
+    const uint32_t n = min(*hp.spill_n, hp.spill_cap);
+    for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n; i += gridDim.x * 256u) hash_place(hp.bp, hp.spill[i]);
+}
+
+hipError_t launch_hash_slices(const HashSliceParams& hp, hipStream_t s) {
+    const uint32_t P = 1u << hp.bits;
+    if (hp.bits < 1 || hp.bits > kSliceMaxBits || (hp.bp.nslots >> hp.bits) > (1ull << kHashSliceSlotBits) ||
+        (hp.bp.nslots >> hp.bits) < 1)
+        return hipErrorInvalidValue;
+    hipError_t e = hipSuccess;
+    if (hp.bp.filt && !hp.bp.filt_via_bytes) {
+        e = launch_fill_u32(hp.bp.filt, (hp.bp.filt_bits + 31) / 32, 0u, s);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(hash_count_kernel, dim3(kHashSliceGrid), dim3(kSliceBlock), 0, s, hp);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    PartParams pp;
+    std::memset(&pp, 0, sizeof pp);
+    pp.n_parts = P;
+    pp.n_regions = kHashSliceGrid;
+    pp.part_hist = hp.hist;
+    pp.part_count = hp.part_count;
+    pp.part_start = hp.part_start;
+    pp.chunk_start = hp.chunk_start;
+    pp.chunk_rows = (uint32_t)kPartChunk;
+    hipLaunchKernelGGL(part_offsets_kernel, dim3(P), dim3(256), 0, s, pp);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(part_scan_kernel, dim3(1), dim3(1024), 0, s, pp);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(hash_scatter_kernel, dim3(kHashSliceGrid), dim3(kSliceBlock),
+                       slice_scatter_rec_lds_bytes(P, false), s, hp);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(hash_slice_kernel, dim3(P), dim3(1024), (size_t)(hp.bp.nslots >> hp.bits) * 8u, s, hp);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(hash_spill_kernel, dim3(64), dim3(256), 0, s, hp);
     return hipGetLastError();
 }
 

@@ -31,6 +31,7 @@ MAX_STAGES = MAX_FACT_PREDS + MAX_JOINS
 MAX_SEGMENTS = 8
 PLAN_SCRATCH_BYTES = 81920
 NOALLOC_SCRATCH_BYTES = 64 << 20
+HASH_SLICE_MIN_ROWS = 1 << 19
 
 OPS = {"eq": 0, "ne": 1, "lt": 2, "le": 3, "gt": 4, "ge": 5, "between": 6}
 TABLES = {"auto": 0, "dense": 1, "hash": 2}
@@ -246,6 +247,16 @@ def dim_required_bytes(desc: SdbDimDesc) -> int:
     return out.value
 
 
+def _workspace_bytes(desc: SdbDimDesc) -> int:
+    """What this module allocates for a table: the required bytes and, for a
+    large hash table, room for its rows as records (9 bytes a row and 4 MiB),
+    with which the library builds it slice by slice."""
+    need = dim_required_bytes(desc)
+    if desc.kind != TABLES["dense"] and desc.n_rows >= HASH_SLICE_MIN_ROWS:
+        need += 9 * desc.n_rows + (4 << 20)
+    return need
+
+
 def dim_desc(key, cols: dict, preds: list, payloads: list, kind: str = "auto",
              load_factor: float = 0.0, dense_budget_bytes: int = 0) -> SdbDimDesc:
     """The C descriptor of one dimension: ``key`` and the values of ``cols``
@@ -285,9 +296,8 @@ def build_dim(key, cols: dict, preds: list, payloads: list, kind: str = "auto",
     """Builds the lookup table of one dimension (arguments as dim_desc)."""
     import torch
     d = dim_desc(key, cols, preds, payloads, kind, load_factor, dense_budget_bytes)
-    need = dim_required_bytes(d)
     if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=key.device)
+        workspace = torch.empty(_workspace_bytes(d), dtype=torch.uint8, device=key.device)
     check_column(workspace, "dimension workspace", device=key.device, dtype="uint8")
     h = SdbDim()
     _check(lib().sdb_build_dim(C.byref(d), _ptr(workspace), workspace.numel(),
@@ -335,7 +345,7 @@ class PreparedDims:
         for i, args in enumerate(inputs):
             self.descs[i] = dim_desc(*args)
         if workspaces is None:
-            workspaces = [torch.empty(dim_required_bytes(self.descs[i]), dtype=torch.uint8,
+            workspaces = [torch.empty(_workspace_bytes(self.descs[i]), dtype=torch.uint8,
                                       device=inputs[i][0].device) for i in range(self.n)]
         if len(workspaces) != self.n:
             raise ValueError(f"{len(workspaces)} workspaces for {self.n} joins")

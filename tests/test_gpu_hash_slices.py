@@ -1,0 +1,117 @@
+"""Hash tables built slice by slice (2^19 rows or more): every row is found
+where linear probing looks for it, the pass filter is as documented, and
+duplicates and uneven hashes are met as by inserts."""
+
+import numpy as np
+import pytest
+
+import datagen
+from gpu_util import assert_same, oracle_rows, require_gpu, run_gpu, upload
+from test_gpu_parity import _bloom_words, _filter_words
+
+pytestmark = pytest.mark.gpu
+
+K = 0x9E3779B1
+
+
+def _dims(keys, seed, groups=300):
+    rng = np.random.default_rng([2607, 7632, 91, seed])
+    return {"key": keys, "flag": rng.integers(0, 2, keys.size, dtype=np.int32),
+            "attr": rng.integers(-5, groups - 5, keys.size, dtype=np.int32)}
+
+
+def _query(lf):
+    return {"fact_preds": [],
+            "joins": [{"fact_key": "key", "dim": "big", "preds": [{"col": "flag", "op": "eq", "lo": 1, "hi": None}],
+                       "payloads": ["attr"], "kind": "hash", "load_factor": lf}],
+            "group_by": [["big", "attr"]], "agg": {"kind": "col", "a": "value", "b": None}}
+
+
+def _build(dim, lf, workspace_extra=True):
+    import torch
+    from paper_2607_07632_amd import sdb
+    require_gpu()
+    cols = {c: torch.from_numpy(a).cuda() for c, a in dim.items()}
+    desc = sdb.dim_desc(*sdb._join_inputs({"big": cols}, {"big": "key"}, _query(lf)["joins"][0]))
+    need = sdb.dim_required_bytes(desc) + (9 * dim["key"].size + (4 << 20) if workspace_extra else 0)
+    ws = torch.full((need,), 0xA5, dtype=torch.uint8, device="cuda")
+    return sdb.build_dims({"big": cols}, {"big": "key"}, _query(lf), workspaces=[ws])[0]
+
+
+def _slots(t):
+    import torch
+    n = int(t.handle.n_slots)
+    off = t.handle.map - t.workspace.data_ptr()
+    return t.workspace[off:off + 8 * n].view(torch.int64).cpu().numpy().view(np.uint64)
+
+
+def _check_table(t, dim):
+    """Every row in exactly one slot, holding its key and code, with no empty
+    slot between its home and there."""
+    slots = _slots(t)
+    n, bits = slots.size, int(t.handle.hash_bits)
+    at = np.flatnonzero(slots)
+    keys = (slots[at] & np.uint64(0xFFFFFFFF)).astype(np.uint32)
+    enc = (slots[at] >> np.uint64(32)).astype(np.uint32)
+    assert at.size == dim["key"].size
+    lo = int(dim["attr"][dim["flag"] == 1].min())
+    want = np.where(dim["flag"] == 1, dim["attr"].astype(np.int64) - lo + 1, 0xFFFFFFFF).astype(np.uint32)
+    order, mine = np.argsort(keys), np.argsort(dim["key"].view(np.uint32))
+    assert np.array_equal(keys[order], dim["key"].view(np.uint32)[mine])
+    assert np.array_equal(enc[order], want[mine])
+    home = ((keys.astype(np.uint64) * np.uint64(K)) & np.uint64(0xFFFFFFFF)) >> np.uint64(32 - bits)
+    dist = (at - home.astype(np.int64)) % n
+    full = np.concatenate([[0], np.cumsum(np.concatenate([slots, slots]) != 0)])
+    assert np.array_equal(full[home.astype(np.int64) + dist] - full[home.astype(np.int64)], dist)
+
+
+@pytest.mark.parametrize("m,lf", [((1 << 19) - 1, 0.5), (1 << 19, 0.5), (700_001, 0.9), (1_300_003, 0.3)])
+def test_slots_and_filter(m, lf):
+    keys = np.random.default_rng(m).choice(1 << 32, m, replace=False).astype(np.uint32).view(np.int32)
+    dim = _dims(keys, m)
+    t = _build(dim, lf)
+    _check_table(t, dim)
+    assert np.array_equal(_filter_words(t), _bloom_words(keys[dim["flag"] == 1], t.handle.filter_bits // 32))
+
+
+def test_without_the_extra_workspace():
+    keys = np.random.default_rng(1).choice(1 << 31, 600_000, replace=False).astype(np.int32)
+    dim = _dims(keys, 1)
+    _check_table(_build(dim, 0.5, workspace_extra=False), dim)
+
+
+def test_uneven_hashes_fall_back_to_inserts():
+    """All hashes in the lower half: the slices there overfill."""
+    inv = pow(K, -1, 1 << 32)
+    h = np.random.default_rng(2).choice(1 << 31, 1 << 19, replace=False).astype(np.uint64)
+    keys = ((h * np.uint64(inv)) & np.uint64(0xFFFFFFFF)).astype(np.uint32).view(np.int32)
+    dim = _dims(keys, 2)
+    t = _build(dim, 0.5)
+    _check_table(t, dim)
+    assert np.array_equal(_filter_words(t), _bloom_words(keys[dim["flag"] == 1], t.handle.filter_bits // 32))
+
+
+def test_duplicates_are_reported():
+    from paper_2607_07632_amd import sdb
+    keys = np.random.default_rng(3).permutation(600_000).astype(np.int32) * 7
+    keys[-1] = keys[5]
+    with pytest.raises(sdb.SdbError) as e:
+        _build(_dims(keys, 3), 0.5)
+    assert e.value.name == "SDB_DUP_KEY"
+
+
+def test_two_sliced_tables_and_a_dense_one_in_one_batch():
+    rng = np.random.default_rng(4)
+    a = rng.choice(1 << 31, 600_000, replace=False).astype(np.int32)
+    b = rng.choice(1 << 31, 530_000, replace=False).astype(np.int32)
+    n = 200_003
+    fact = {"ka": a[rng.integers(0, a.size, n)], "kb": b[rng.integers(0, b.size, n)],
+            "kc": rng.integers(0, 1000, n, dtype=np.int32), "v": rng.integers(-10**6, 10**6, n, dtype=np.int32)}
+    dims = {"a": _dims(a, 5, 20), "b": _dims(b, 6, 30), "c": _dims(np.arange(1000, dtype=np.int32), 7, 4)}
+    joins = [{"fact_key": "k" + d, "dim": d, "preds": [{"col": "flag", "op": "eq", "lo": 1, "hi": None}],
+              "payloads": ["attr"], "kind": "auto"} for d in "abc"]
+    w = datagen.Workload("two sliced", n, fact, dims, {d: "key" for d in "abc"},
+                         {"fact_preds": [], "joins": joins, "group_by": [[d, "attr"] for d in "abc"],
+                          "agg": {"kind": "col", "a": "v", "b": None}})
+    got, _ = run_gpu(w, dev=upload(w))
+    assert_same(got.as_rows(), oracle_rows(w), "two sliced tables")
