@@ -956,6 +956,8 @@ bool columns_aligned(const sdb_query* q, const sdb_plan* plan) {
 }
 
 constexpr int kDefaultIpt = 2;
+constexpr int64_t kRankMinRows = 8'000'000;
+constexpr int64_t kRankMinRowsLookups = 50'000'000;
 constexpr bool kAutoEager = false;
 // a 128-byte line holds 32 rows: at 2% live rows about half its lines are still read
 constexpr double kEagerMinLive = 0.02;
@@ -1921,8 +1923,14 @@ SDB_API sdb_status sdb_plan_star_query(const sdb_query* q, void* scratch, int64_
     // than 16 waves per CU anyway (c3: fused kernel 2.234 -> 2.195 ms, 21M
     // deferred gathers spared), not when a lookup-heavy plan runs one item per
     // lane at 32 waves per CU (c4: 1.67 -> 2.67 ms).
+    // Building and staging them costs about 12 us, so they need rows enough:
+    // without another device-memory lookup they pay from about 8M rows on (a
+    // join of 4M rows 30.5 us with them, 27.4 without; 16M 54.5 and 61.4), with
+    // one from about 50M (c3's shape: 30M rows 189 and 181; 60M 315 and 319).
+    const int64_t rank_rows = device_lookups == 0 ? kRankMinRows : kRankMinRowsLookups;
     const bool want_rank = q->force_lds == 3 ||
-                           (q->force_lds == 0 && (device_lookups == 0 || (plan->ipt == 2 && plan->vector)));
+                           (q->force_lds == 0 && q->n_fact >= rank_rows &&
+                            (device_lookups == 0 || (plan->ipt == 2 && plan->vector)));
     if (want_rank && plan->vector && plan->ipt <= 2 && plan->eager == 0 &&
         (q->force_block == 0 || q->force_block == kBigBlock)) {
         for (int s = 0; s < n; ++s) {
@@ -2227,6 +2235,7 @@ SDB_API sdb_status sdb_run_star_query(const sdb_query* q, const sdb_plan* plan, 
         p3.ring_off = p.ring_off;
         p = p3;
     }
+    bool zeroed = false;
     {
         // the rank tables of LDS_RANK stages and the coarse bitmaps of
         // LDS_COARSE stages, derived from their pass bitmaps and maps
@@ -2248,6 +2257,7 @@ SDB_API sdb_status sdb_run_star_query(const sdb_query* q, const sdb_plan* plan, 
             if (plan->stage_lds[st_i] != LDS_RANK) continue;
             const sdb_dim* d = q->joins[plan->stage_index[st_i]].dim;
             RankParams rp;
+            std::memset(&rp, 0, sizeof rp);
             rp.bits = (const uint32_t*)d->bits;
             rp.map = d->map;
             rp.width = d->width;
@@ -2258,12 +2268,20 @@ SDB_API sdb_status sdb_run_star_query(const sdb_query* q, const sdb_plan* plan, 
             off += scratch_part(lds_codes_bytes(d));
             p.st[st_i].rank = rp.prefix;
             p.st[st_i].codes = rp.codes;
-            if (q->n_fact > 0) SDB_HIP(launch_rank_build(rp, s), "rank table launch");
+            if (q->n_fact > 0) {
+                if (!plan->xcd_copies && !zeroed) {   // the outputs are zeroed beside
+                    rp.zero_a = (unsigned long long*)sums;
+                    rp.zero_b = (unsigned long long*)counts;
+                    rp.zero_n = plan->n_groups;
+                    zeroed = true;
+                }
+                SDB_HIP(launch_rank_build(rp, s), "rank table launch");
+            }
         }
     }
     if (plan->xcd_copies) {
         SDB_HIP(launch_fill_u64((unsigned long long*)term_base, term_scratch / 8, s), "copy fill");
-    } else {
+    } else if (!zeroed) {
         SDB_HIP(launch_zero_pair((unsigned long long*)sums, (unsigned long long*)counts, plan->n_groups, s),
                 "output fill");
     }

@@ -27,6 +27,8 @@ constexpr int kXcdCopies = 8;            // XCDs of an MI355X: private group-tab
 constexpr int kFinBlock = 256;           // finalize: threads per block
 constexpr int kFinPerThread = 4;         // finalize: groups per thread
 constexpr int kFinGroupsPerBlock = kFinBlock * kFinPerThread;
+constexpr uint64_t kFinOneGroups = 8192; // finalize: at most this many groups in one block's one kernel
+constexpr int64_t kFinMaxPrefix = 4096;  // ... and this many blocks that add up the counts before their own
 constexpr int kDenseSlack = 1024;        // dense limit: key range <= max(2 * n_rows, 1024)
 
 enum StageKind : int32_t { ST_PRED = 0, ST_DENSE = 1, ST_HASH = 2 };
@@ -172,6 +174,10 @@ struct RankParams {
     uint32_t nslots;
     uint32_t* prefix;          // (nslots + 63) / 64 entries: passing slots before each 64-slot group
     void* codes;               // codes of the passing slots in slot order
+    // the outputs to zero beside (zero_n groups; 0: none)
+    unsigned long long* zero_a;
+    unsigned long long* zero_b;
+    uint64_t zero_n;
 };
 
 struct FusedParams {

@@ -686,66 +686,76 @@ __device__ __forceinline__ uint32_t rank_word(const RankParams& rp, uint32_t w) 
     return w < (rp.nslots + 31u) / 32u ? rp.bits[w] : 0u;
 }
 
-// One block of 1024 threads: prefix[g] = passing slots in 64-slot groups
-// before g (exclusive scan of the groups' popcounts).
-__global__ void __launch_bounds__(1024) rank_prefix_kernel(RankParams rp) {
-    __shared__ uint32_t wsum[16];
-    const uint32_t n64 = (rp.nslots + 63u) / 64u;
-    constexpr uint32_t kPer = kRankGroups / 1024;
-    const uint32_t g0 = threadIdx.x * kPer;
-    uint32_t c[kPer];
-    uint32_t loc = 0;
-#pragma unroll
-    for (uint32_t k = 0; k < kPer; ++k) {
-        const uint32_t g = g0 + k;
-        c[k] = g < n64 ? (uint32_t)(__popc(rank_word(rp, 2 * g)) + __popc(rank_word(rp, 2 * g + 1))) : 0u;
-        loc += c[k];
+constexpr uint32_t kRankWords = 256;   // bitmap words per block, one per thread
+
+// Block b < rank_blocks: words 256 b .. of the bitmap. It counts the passing
+// slots of all words before (at most 8,192 words, an L2 read of 32 KB), scans
+// its own, writes the 64-slot groups' counts and stores the passing slots'
+// codes at their ranks. The other blocks zero the outputs: one launch in place
+// of three (about 4.5 us each when launches follow one another).
+__global__ void __launch_bounds__(256) rank_build_kernel(RankParams rp, uint32_t rank_blocks) {
+    if (blockIdx.x >= rank_blocks) {
+        const uint64_t stride = (uint64_t)(gridDim.x - rank_blocks) * 256u;
+        for (uint64_t i = (uint64_t)(blockIdx.x - rank_blocks) * 256u + threadIdx.x; i < rp.zero_n; i += stride) {
+            rp.zero_a[i] = 0ull;
+            rp.zero_b[i] = 0ull;
+        }
+        return;
     }
+    __shared__ uint32_t wbefore[4], wown[4], wbits[kRankWords], wrank[kRankWords];
+    const uint32_t w0 = blockIdx.x * kRankWords, w = w0 + threadIdx.x;
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    uint32_t x = loc;
+    uint32_t before = 0;
+    const v4u* quads = reinterpret_cast<const v4u*>(rp.bits);   // (whole quads: w0 is a multiple of 256)
+#pragma unroll 8
+    for (uint32_t i = threadIdx.x; i < w0 / 4u; i += kRankWords) {
+        const v4u x = quads[i];
+        before += (uint32_t)(__popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w));
+    }
+    for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off, 64);
+    const uint32_t bits = rank_word(rp, w);
+    const uint32_t own = (uint32_t)__popc(bits);
+    uint32_t x = own;
     for (uint32_t off = 1; off < 64u; off <<= 1) {
         const uint32_t y = __shfl_up(x, off, 64);
         if (lane >= off) x += y;
     }
-    if (lane == 63u) wsum[wave] = x;
-    __syncthreads();
-    uint32_t run = x - loc;
-    for (uint32_t w = 0; w < wave; ++w) run += wsum[w];
-#pragma unroll
-    for (uint32_t k = 0; k < kPer; ++k) {
-        const uint32_t g = g0 + k;
-        if (g < n64) rp.prefix[g] = run;
-        run += c[k];
+    if (lane == 63u) {
+        wbefore[wave] = before;
+        wown[wave] = x;
     }
-}
-
-// One thread per bitmap word: the word's passing slots store their codes at
-// their ranks.
-__global__ void __launch_bounds__(256) rank_codes_kernel(RankParams rp) {
-    const uint32_t n_words = (rp.nslots + 31u) / 32u;
-    const uint32_t w = blockIdx.x * blockDim.x + threadIdx.x;
-    if (w >= n_words) return;
-    uint32_t bits = rp.bits[w];
-    uint32_t r = rp.prefix[w >> 1] + ((w & 1u) ? (uint32_t)__popc(rp.bits[w - 1]) : 0u);
-    while (bits) {
-        const uint32_t b = (uint32_t)__ffs(bits) - 1u;
-        bits &= bits - 1u;
-        const uint32_t slot = w * 32u + b;
-        if (rp.width == 1) static_cast<uint8_t*>(rp.codes)[r] = static_cast<const uint8_t*>(rp.map)[slot];
-        else if (rp.width == 2) static_cast<uint16_t*>(rp.codes)[r] = static_cast<const uint16_t*>(rp.map)[slot];
-        else static_cast<uint32_t*>(rp.codes)[r] = static_cast<const uint32_t*>(rp.map)[slot];
-        ++r;
+    __syncthreads();
+    uint32_t r = x - own + wbefore[0] + wbefore[1] + wbefore[2] + wbefore[3];
+    for (uint32_t v = 0; v < wave; ++v) r += wown[v];
+    if ((w & 1u) == 0u && w / 2u < (rp.nslots + 63u) / 64u) rp.prefix[w / 2u] = r;
+    wbits[threadIdx.x] = bits;
+    wrank[threadIdx.x] = r;
+    __syncthreads();
+    // a thread per slot, all its 32 slots' codes read together
+    uint32_t c[32];
+#pragma unroll
+    for (uint32_t u = 0; u < 32u; ++u) {
+        const uint32_t slot = min(w0 * 32u + u * 256u + threadIdx.x, rp.nslots - 1u);
+        if (rp.width == 1) c[u] = static_cast<const uint8_t*>(rp.map)[slot];
+        else if (rp.width == 2) c[u] = static_cast<const uint16_t*>(rp.map)[slot];
+        else c[u] = static_cast<const uint32_t*>(rp.map)[slot];
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < 32u; ++u) {   // (bits past the last slot are clear)
+        const uint32_t i = u * 8u + (threadIdx.x >> 5), bit = threadIdx.x & 31u;
+        if (!((wbits[i] >> bit) & 1u)) continue;
+        const uint32_t to = wrank[i] + (uint32_t)__popc(wbits[i] & ((1u << bit) - 1u));
+        if (rp.width == 1) static_cast<uint8_t*>(rp.codes)[to] = (uint8_t)c[u];
+        else if (rp.width == 2) static_cast<uint16_t*>(rp.codes)[to] = (uint16_t)c[u];
+        else static_cast<uint32_t*>(rp.codes)[to] = c[u];
     }
 }
 
 hipError_t launch_rank_build(const RankParams& rp, hipStream_t s) {
-    if (rp.nslots == 0) return hipSuccess;
-    if ((rp.nslots + 63u) / 64u > kRankGroups) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(rank_prefix_kernel, dim3(1), dim3(1024), 0, s, rp);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const uint32_t n_words = (rp.nslots + 31u) / 32u;
-    hipLaunchKernelGGL(rank_codes_kernel, dim3((n_words + 255u) / 256u), dim3(256), 0, s, rp);
+    if (rp.nslots == 0 || (rp.nslots + 63u) / 64u > kRankGroups) return hipErrorInvalidValue;
+    const uint32_t blocks = ((rp.nslots + 31u) / 32u + kRankWords - 1u) / kRankWords;
+    const uint32_t zero = rp.zero_n ? (uint32_t)std::min<uint64_t>(1024u, (rp.zero_n + 255u) / 256u) : 0u;
+    hipLaunchKernelGGL(rank_build_kernel, dim3(blocks + zero), dim3(256), 0, s, rp, blocks);
     return hipGetLastError();
 }
 
@@ -2536,10 +2546,34 @@ __global__ void __launch_bounds__(1024) fin_scan_kernel(FinalizeParams fp) {
     if (threadIdx.x == 0) fp.out_n[0] = carry;
 }
 
-__global__ void __launch_bounds__(kFinBlock) fin_scatter_kernel(FinalizeParams fp) {
+// Group g of the table goes to row o of the result.
+__device__ __forceinline__ void fin_write(const FinalizeParams& fp, uint64_t g, uint64_t o) {
+    for (int q = 0; q < fp.n_keys; ++q)
+        fp.out_keys[o * fp.n_keys + q] = (int32_t)(((uint32_t)g / fp.stride[q]) % fp.radix[q]) + fp.key_min[q];
+    fp.out_sums[o] = fp.sums[g];
+    fp.out_counts[o] = fp.counts[g];
+}
+
+// `scanned`: block_off holds offsets (fin_scan_kernel); else the blocks'
+// counts, and every block adds up those before its own (at most
+// kFinMaxPrefix: 32 KB from L2, cheaper than a launch for the scan).
+__global__ void __launch_bounds__(kFinBlock) fin_scatter_kernel(FinalizeParams fp, bool scanned) {
     __shared__ unsigned int wcnt[kFinBlock / 64];
     __shared__ long long run;
-    if (threadIdx.x == 0) run = fp.block_off[blockIdx.x];
+    __shared__ unsigned long long part[kFinBlock / 64];
+    if (scanned) {
+        if (threadIdx.x == 0) run = fp.block_off[blockIdx.x];
+    } else {
+        unsigned long long c = 0;
+        for (uint32_t i = threadIdx.x; i < blockIdx.x; i += kFinBlock) c += (unsigned long long)fp.block_off[i];
+        c = wave_sum_u64(c);
+        if ((threadIdx.x & 63u) == 0u) part[threadIdx.x >> 6] = c;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            run = (long long)(part[0] + part[1] + part[2] + part[3]);
+            if (blockIdx.x == gridDim.x - 1u) fp.out_n[0] = run + fp.block_off[blockIdx.x];
+        }
+    }
     __syncthreads();
     const uint64_t base = (uint64_t)blockIdx.x * kFinGroupsPerBlock;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -2556,28 +2590,66 @@ __global__ void __launch_bounds__(kFinBlock) fin_scatter_kernel(FinalizeParams f
             if (w < wave) before += wcnt[w];
             total += wcnt[w];
         }
-        if (present) {
-            const long long o = run + before;
-            for (int q = 0; q < fp.n_keys; ++q)
-                fp.out_keys[o * fp.n_keys + q] =
-                    (int32_t)(((uint32_t)g / fp.stride[q]) % fp.radix[q]) + fp.key_min[q];
-            fp.out_sums[o] = fp.sums[g];
-            fp.out_counts[o] = fp.counts[g];
-        }
+        if (present) fin_write(fp, g, (uint64_t)run + before);
         __syncthreads();
         if (threadIdx.x == 0) run += total;
         __syncthreads();
     }
 }
 
+// Up to kFinOneGroups groups by one block: thread t holds groups k * 1024 + t,
+// whose counts it loads together; a group's place is the number of groups
+// present before it, from the waves' ballots.
+__global__ void __launch_bounds__(1024) fin_one_kernel(FinalizeParams fp) {
+    constexpr int R = (int)(kFinOneGroups / 1024);
+    __shared__ uint32_t cnt[R * 16];
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    const int rounds = (int)((fp.n_groups + 1023u) / 1024u);
+    unsigned long long m[R];
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        m[k] = 0ull;
+        if (k < rounds) {
+            m[k] = __ballot(group_present(fp, (uint64_t)k * 1024u + threadIdx.x));
+            if (lane == 0) cnt[k * 16 + wave] = (uint32_t)__popcll(m[k]);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < 64u) {   // exclusive scan of the (at most 128) wave counts by one wave, two a lane
+        const uint32_t n = (uint32_t)rounds * 16u;
+        const uint32_t a = 2u * lane < n ? cnt[2u * lane] : 0u, b = 2u * lane + 1u < n ? cnt[2u * lane + 1u] : 0u;
+        uint32_t x = a + b;
+        for (uint32_t off = 1; off < 64u; off <<= 1) {
+            const uint32_t y = __shfl_up(x, off, 64);
+            if (lane >= off) x += y;
+        }
+        if (2u * lane < n) cnt[2u * lane] = x - a - b;
+        if (2u * lane + 1u < n) cnt[2u * lane + 1u] = x - b;
+        if (lane == 63u) fp.out_n[0] = x;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < R; ++k)
+        if ((m[k] >> lane) & 1ull)
+            fin_write(fp, (uint64_t)k * 1024u + threadIdx.x,
+                      cnt[k * 16 + wave] + (uint32_t)__popcll(m[k] & ((1ull << lane) - 1ull)));
+}
+
 hipError_t launch_finalize(const FinalizeParams& fp, hipStream_t s) {
+    if (fp.n_groups <= kFinOneGroups) {
+        hipLaunchKernelGGL(fin_one_kernel, dim3(1), dim3(1024), 0, s, fp);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(fin_count_kernel, dim3((unsigned)fp.n_blocks), dim3(kFinBlock), 0, s, fp);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(fin_scan_kernel, dim3(1), dim3(1024), 0, s, fp);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(fin_scatter_kernel, dim3((unsigned)fp.n_blocks), dim3(kFinBlock), 0, s, fp);
+    const bool scan = fp.n_blocks > kFinMaxPrefix;
+    if (scan) {
+        hipLaunchKernelGGL(fin_scan_kernel, dim3(1), dim3(1024), 0, s, fp);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(fin_scatter_kernel, dim3((unsigned)fp.n_blocks), dim3(kFinBlock), 0, s, fp, scan);
     return hipGetLastError();
 }
 
