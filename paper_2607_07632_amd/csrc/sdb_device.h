@@ -63,6 +63,36 @@ __device__ __forceinline__ uint32_t hash_slot(const StageDev& S, int32_t k) {
     return ((uint32_t)k * 0x9E3779B1u) >> S.hshift & S.hmask;
 }
 
+// Pass filter of a hash table's keys. SDB_FILTER_BITMAP: bit k - key_min of
+// the key range. SDB_FILTER_BLOOM: three bits of one 32-bit word, the word
+// and the bits from two mixes of the key (a blocked Bloom filter: one word
+// read per test).
+// The key mix is MurmurHash3's 32-bit finalizer.
+__device__ __forceinline__ uint32_t filter_mix(int32_t k) {
+    uint32_t m = (uint32_t)k;
+    m = (m ^ (m >> 16)) * 0x85EBCA6Bu;
+    m ^= m >> 13;
+    m *= 0xC2B2AE35u;
+    return m ^ (m >> 16);
+}
+
+// Word index and bit mask of key k in a filter of `nbits` bits; false when a
+// bitmap's key range does not hold k.
+__device__ __forceinline__ bool filter_slot(int32_t kind, uint64_t nbits, int32_t kmin, int32_t k, uint32_t& word,
+                                            uint32_t& mask) {
+    if (kind == SDB_FILTER_BITMAP) {
+        const uint32_t idx = (uint32_t)k - (uint32_t)kmin;
+        word = idx >> 5;
+        mask = 1u << (idx & 31u);
+        return (uint64_t)idx < nbits;
+    }
+    const uint32_t m = filter_mix(k);
+    const uint32_t t = ((m << 16) | (m >> 16)) * 0x9E3779B1u;
+    word = m & (uint32_t)((nbits >> 5) - 1u);
+    mask = (1u << (t >> 27)) | (1u << ((t >> 22) & 31u)) | (1u << ((t >> 17) & 31u));
+    return true;
+}
+
 // Resolves a hash probe whose first slot value is `slot`; returns the code or
 // the sentinel. Linear probing; at most nslots slots are inspected.
 __device__ __forceinline__ uint32_t hash_resolve(const StageDev& S, int32_t k, uint32_t h,

@@ -347,6 +347,90 @@ __device__ __forceinline__ void stage_hash(const StageDev& S, const int32_t (&x)
     }
 }
 
+// A hash stage's pass filter (StageDev says where it stands): rows it rejects die.
+template <int W, int IPT>
+__device__ __forceinline__ void stage_filter(const StageDev& S, const int32_t (&x)[IPT][W], bool (&al)[IPT][W]) {
+    const uint32_t* words = static_cast<const uint32_t*>(S.bits);
+    uint32_t w[IPT][W], m[IPT][W];
+    SDB_ROWS(j, r) {
+        const bool in = filter_slot(S.coarse_shift, S.win_slots, S.kmin, x[j][r], w[j][r], m[j][r]);
+        al[j][r] = al[j][r] && in;
+        w[j][r] = words[al[j][r] ? w[j][r] : 0u];
+    }
+    SDB_ROWS(j, r) al[j][r] = al[j][r] && (w[j][r] & m[j][r]) == m[j][r];
+}
+
+// The hash probe of the instances for plans that make one (UNR < 0; the others
+// keep stage_hash, which they reach only when their shape is forced: this one's
+// code in them slowed plans without a hash table: c3's shape 2.17 -> 2.42 ms). An item's rows go on together, two slots a turn, until none of the wave's is
+// left, so a turn costs one table latency for all of them (150M rows through
+// L2 slices: 2.41 -> 1.94 ms). Where the host asks for it, a row first tests the
+// table's pass filter, a read that hits L2 where the probe would not:
+// a probe of a table past L2 runs at about 54G rows/s, a filter read at 215G.
+template <int W, int IPT, bool PAIR>
+__device__ __forceinline__ void stage_probe(const StageDev& S, const int32_t (&x)[IPT][W], bool (&al)[IPT][W],
+                                           uint32_t (&gid)[IPT][W]) {
+    const unsigned long long* tab = static_cast<const unsigned long long*>(S.map);
+    constexpr int HJ = 1;
+#pragma unroll
+    for (int j0 = 0; j0 < IPT; j0 += HJ) {
+        uint32_t h[HJ][W], c[HJ][W];
+        bool pend[HJ][W];
+#pragma unroll
+        for (int jj = 0; jj < HJ; ++jj)
+#pragma unroll
+            for (int r = 0; r < W; ++r) {
+                h[jj][r] = hash_slot(S, x[j0 + jj][r]);
+                c[jj][r] = S.sentinel;
+                pend[jj][r] = al[j0 + jj][r];
+            }
+        for (uint32_t it = 0; it < S.nslots; it += 2u) {   // (a table has an empty slot, which ends every chain)
+            unsigned long long sl[HJ][W], sn[HJ][W];
+#pragma unroll
+            for (int jj = 0; jj < HJ; ++jj)
+#pragma unroll
+                for (int r = 0; r < W; ++r) {
+                    sl[jj][r] = 0ull;
+                    sn[jj][r] = 0ull;
+                    if (pend[jj][r]) {
+                        // a slot and the next one (mostly the same cache line)
+                        if (PAIR && h[jj][r] != S.hmask) {
+                            const u64x2 pr = *reinterpret_cast<const u64x2_a8*>(tab + h[jj][r]);
+                            sl[jj][r] = pr.x;
+                            sn[jj][r] = pr.y;
+                        } else {
+                            sl[jj][r] = tab[h[jj][r]];
+                            sn[jj][r] = tab[(h[jj][r] + 1u) & S.hmask];
+                        }
+                    }
+                }
+            bool more = false;
+#pragma unroll
+            for (int jj = 0; jj < HJ; ++jj)
+#pragma unroll
+                for (int r = 0; r < W; ++r) {
+                    const uint32_t k = (uint32_t)x[j0 + jj][r];
+                    const uint32_t e0 = (uint32_t)(sl[jj][r] >> 32), e1 = (uint32_t)(sn[jj][r] >> 32);
+                    const bool hit0 = e0 != 0u && (uint32_t)sl[jj][r] == k;
+                    const bool hit1 = e0 != 0u && e1 != 0u && (uint32_t)sn[jj][r] == k;
+                    if (pend[jj][r] && (hit0 || hit1)) c[jj][r] = (hit0 ? e0 : e1) - 1u;   // a filtered row: the sentinel
+                    pend[jj][r] = pend[jj][r] && e0 != 0u && e1 != 0u && !hit0 && !hit1;
+                    h[jj][r] = (h[jj][r] + 2u) & S.hmask;
+                    more = more || pend[jj][r];
+                }
+            if (!__any(more)) break;
+        }
+#pragma unroll
+        for (int jj = 0; jj < HJ; ++jj)
+#pragma unroll
+            for (int r = 0; r < W; ++r) {
+                al[j0 + jj][r] = al[j0 + jj][r] && c[jj][r] < S.sentinel;
+                if (S.gk_mode == GK_ONE) gid[j0 + jj][r] += c[jj][r] * S.gk_stride[0];
+                else if (S.gk_mode == GK_GENERAL) gid[j0 + jj][r] += code_contribution(S, c[jj][r]);
+            }
+    }
+}
+
 // The deferred stage's codes for the rows still live (dead rows read slot 0,
 // a line every such row shares).
 template <int W, int IPT>
@@ -370,12 +454,19 @@ __device__ __forceinline__ bool wave_has_live(const bool (&al)[IPT][W]) {
 
 // One stage of the plan for the current items: fetch its column, then apply
 // its predicate or lookup.
-template <int W, int IPT, bool EG>
+template <int W, int IPT, bool EG, bool PROBE = false>
 __device__ __forceinline__ void run_stage(const FusedParams& p, const unsigned char* lds, const StageDev& S,
                                           const int64_t (&item)[IPT], bool (&al)[IPT][W], uint32_t (&gid)[IPT][W],
                                           uint32_t (&didx)[IPT][W], const int32_t (&eg)[kMaxEager][IPT][W]) {
     int32_t x[IPT][W];
     fetch_column<W, IPT, EG>(p, S.col, S.eg_slot, item, al, eg, x);
+    if constexpr (PROBE) {   // (not a case below: even an empty one there slowed the other instances)
+        if (S.op == OP_HASH_FILTER) {
+            stage_filter<W, IPT>(S, x, al);
+            if (wave_has_live<W, IPT>(al)) stage_probe<W, IPT, false>(S, x, al, gid);
+            return;
+        }
+    }
     switch (S.op) {
         case OP_PRED:
             SDB_ROWS(j, r) al[j][r] = al[j][r] && range_pass(S.test, x[j][r]);
@@ -387,8 +478,14 @@ __device__ __forceinline__ void run_stage(const FusedParams& p, const unsigned c
         case OP_MAP1: stage_map<W, IPT, 1, false>(S, lds, x, al, gid); break;
         case OP_MAP2: stage_map<W, IPT, 2, false>(S, lds, x, al, gid); break;
         case OP_MAP4: stage_map<W, IPT, 4, false>(S, lds, x, al, gid); break;
-        case OP_HASH: stage_hash<W, IPT, false>(S, x, al, gid); break;
-        case OP_HASH_PAIR: stage_hash<W, IPT, true>(S, x, al, gid); break;
+        case OP_HASH:
+            if constexpr (PROBE) stage_probe<W, IPT, false>(S, x, al, gid);
+            else stage_hash<W, IPT, false>(S, x, al, gid);
+            break;
+        case OP_HASH_PAIR:
+            if constexpr (PROBE) stage_probe<W, IPT, true>(S, x, al, gid);
+            else stage_hash<W, IPT, true>(S, x, al, gid);
+            break;
         case OP_LDS_RANK1: stage_rank<W, IPT, 1>(S, lds, x, al, gid); break;
         case OP_LDS_RANK2: stage_rank<W, IPT, 2>(S, lds, x, al, gid); break;
         case OP_LDS_RANK4: stage_rank<W, IPT, 4>(S, lds, x, al, gid); break;
@@ -431,7 +528,7 @@ __device__ __forceinline__ void process_items(const FusedParams& p, const unsign
     } else {
         for (int s = 0; s < p.nstages; ++s) {
             if (!wave_has_live<W, IPT>(al)) return;
-            run_stage<W, IPT, EG>(p, lds, p.st[s], item, al, gid, didx, eg);
+            run_stage<W, IPT, EG, (UNR < 0)>(p, lds, p.st[s], item, al, gid, didx, eg);
         }
     }
     if (!wave_has_live<W, IPT>(al)) return;
@@ -571,7 +668,7 @@ __global__ void __launch_bounds__(LB) star_fused_kernel(FusedParams kernel_args)
         if (blockIdx.x == gridDim.x - 1) {
             int64_t row[1] = {n_items * W + (int64_t)threadIdx.x};
             bool al1[1][1] = {{row[0] < n_rows}};
-            process_items<1, 1, TERM, false>(p, lds, row, al1, ts);
+            process_items<1, 1, TERM, false, (UNR < 0 ? -1 : 0)>(p, lds, row, al1, ts);
         }
     }
 
@@ -643,6 +740,8 @@ const void* pick_fused_vec(int ipt, int terminal);
 const void* pick_fused_big(int ipt, int terminal);
 // 4-row items with eager column loads, ipt 1 or 2, launch bound kMaxBlock;
 const void* pick_fused_eager(int ipt, int terminal);
+// 4-row items for plans with a hash probe (UNR < 0), ipt 1 or 2, blocks of up to kBigBlock;
+const void* pick_fused_probe(int ipt, int terminal);
 // 1-row items, ipt 1, 2 or 4, launch bound kMaxBlock.
 const void* pick_fused_rows(int ipt, int terminal);
 

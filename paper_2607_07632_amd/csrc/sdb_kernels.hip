@@ -436,36 +436,6 @@ __global__ void __launch_bounds__(256) dense_bits_kernel(BuildBatch kernel_args)
     }
 }
 
-// Pass filter of a hash table's keys. SDB_FILTER_BITMAP: bit k - key_min of
-// the key range. SDB_FILTER_BLOOM: three bits of one 32-bit word, the word
-// and the bits from two mixes of the key (a blocked Bloom filter: one word
-// read per test).
-// The key mix is MurmurHash3's 32-bit finalizer.
-__device__ __forceinline__ uint32_t filter_mix(int32_t k) {
-    uint32_t m = (uint32_t)k;
-    m = (m ^ (m >> 16)) * 0x85EBCA6Bu;
-    m ^= m >> 13;
-    m *= 0xC2B2AE35u;
-    return m ^ (m >> 16);
-}
-
-// Word index and bit mask of key k in a filter of `nbits` bits; false when a
-// bitmap's key range does not hold k.
-__device__ __forceinline__ bool filter_slot(int32_t kind, uint64_t nbits, int32_t kmin, int32_t k, uint32_t& word,
-                                            uint32_t& mask) {
-    if (kind == SDB_FILTER_BITMAP) {
-        const uint32_t idx = (uint32_t)k - (uint32_t)kmin;
-        word = idx >> 5;
-        mask = 1u << (idx & 31u);
-        return (uint64_t)idx < nbits;
-    }
-    const uint32_t m = filter_mix(k);
-    const uint32_t t = ((m << 16) | (m >> 16)) * 0x9E3779B1u;
-    word = m & (uint32_t)((nbits >> 5) - 1u);
-    mask = (1u << (t >> 27)) | (1u << ((t >> 22) & 31u)) | (1u << ((t >> 17) & 31u));
-    return true;
-}
-
 // The slot value of dimension row i: {key, code + 1 | 0xFFFFFFFF}.
 __device__ __forceinline__ unsigned long long hash_slot_value(const BuildParams& bp, int64_t i) {
     const uint32_t enc = dim_row_passes(bp, i) ? dim_row_code(bp, i) + 1u : 0xFFFFFFFFu;
@@ -857,6 +827,7 @@ hipError_t launch_xcd_merge(const unsigned long long* xtab, int copies, uint64_t
 // loop written out kUnrollStages times for 4-row items, 2 items per lane,
 // blocks of kMaxBlock or kBigBlock and no eager loads.
 static const void* pick_fused(int vector, int ipt, int terminal, int eager, int block, int unroll) {
+    if (unroll < 0) return vector && eager <= 0 && block <= kBigBlock ? pick_fused_probe(ipt, terminal) : nullptr;
     if (unroll) {
         if (!vector || ipt != 2 || eager > 0) return nullptr;
         if (block <= kMaxBlock) return pick_fused_unrolled(terminal);
@@ -880,7 +851,7 @@ int fused_blocks_per_cu(int vector, int ipt, int terminal, int eager, int block,
 
 hipError_t launch_fused(const FusedParams& p, int vector, int ipt, int terminal, int eager, int unroll, int grid,
                         int block, size_t lds_bytes, hipStream_t s) {
-    if (unroll && p.nstages > kUnrollStages) return hipErrorInvalidValue;
+    if (unroll > 0 && p.nstages > kUnrollStages) return hipErrorInvalidValue;
     const void* fn = pick_fused(vector, ipt, terminal, eager, block, unroll);
     if (!fn) return hipErrorInvalidValue;
     void* args[] = {const_cast<FusedParams*>(&p)};
