@@ -2339,6 +2339,15 @@ __global__ void __launch_bounds__(kSliceBlock) hash_count_kernel(HashSliceParams
 }
 
 __global__ void __launch_bounds__(kSliceBlock) hash_scatter_kernel(HashSliceParams hp) {
+    // a slice with more rows than slots cannot be built: no pass does anything
+    // from here on, and the host builds the table with inserts
+    bool over = false;
+    for (uint32_t q = threadIdx.x; q < 1u << hp.bits; q += kSliceBlock)
+        over = over || hp.part_count[q] > (uint32_t)(hp.bp.nslots >> hp.bits);
+    if (__syncthreads_or(over)) {
+        if (threadIdx.x == 0) atomicOr(&hp.bp.stats->dup, kHashSliceRetry);
+        return;
+    }
     SliceParams sp;
     sp.n = hp.bp.n;
     sp.rows_per_block = hp.rows_per_block;
@@ -2388,10 +2397,10 @@ __global__ void __launch_bounds__(1024) hash_slice_kernel(HashSliceParams hp) {
     const BuildParams& bp = hp.bp;
     const uint32_t q = blockIdx.x, per = (uint32_t)(bp.nslots >> hp.bits);
     const uint32_t r0 = hp.part_start[q], n = hp.part_start[q + 1] - r0;
-    if (n > per) {   // cannot fit: the host builds this table with inserts
-        if (threadIdx.x == 0) atomicOr(&bp.stats->dup, kHashSliceRetry);
+    // (read by one thread: a block that spills past the capacity sets the flag meanwhile)
+    if (__syncthreads_or(threadIdx.x == 0 && (__hip_atomic_load(&bp.stats->dup, __ATOMIC_RELAXED,
+                                                                __HIP_MEMORY_SCOPE_AGENT) & kHashSliceRetry)))
         return;
-    }
     for (uint32_t i = threadIdx.x; i < per; i += 1024u) slots[i] = 0ull;
     __syncthreads();
     constexpr int U = 8;
@@ -2427,8 +2436,11 @@ __global__ void __launch_bounds__(1024) hash_slice_kernel(HashSliceParams hp) {
     for (uint32_t i = threadIdx.x; i < per; i += 1024u) tab[i] = slots[i];
 }
 
-// The rows past their slices' ends, once every slice is written.
+// The rows past their slices' ends, once every slice is written. Not where the
+// slices were given up: the table then holds what the workspace held, and
+// probing it for an empty slot could walk all of it for every row.
 __global__ void __launch_bounds__(256) hash_spill_kernel(HashSliceParams hp) {
+    if (hp.bp.stats->dup & kHashSliceRetry) return;
     const uint32_t n = min(*hp.spill_n, hp.spill_cap);
     for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n; i += gridDim.x * 256u) hash_place(hp.bp, hp.spill[i]);
 }

@@ -91,6 +91,26 @@ def test_uneven_hashes_fall_back_to_inserts():
     assert np.array_equal(_filter_words(t), _bloom_words(keys[dim["flag"] == 1], t.handle.filter_bits // 32))
 
 
+def test_full_slices_between_overfull_ones():
+    """Slices of 4,096 slots: each odd one holds more rows than slots, each even
+    one 3,000 rows in its last half, which spill, so no pass may probe a table
+    that holds what the workspace held (0xA5) before the inserts."""
+    rng = np.random.default_rng(8)
+    per = 1 << 12
+    h = []
+    for q in range(0, 150, 2):
+        h.append((q * per + per // 2) * 4096 + rng.choice(per // 2 * 4096, 3000, replace=False))
+        h.append((q + 1) * per * 4096 + rng.choice(per * 4096, per + 50, replace=False))
+    h = np.concatenate(h).astype(np.uint64)
+    assert h.size >= 1 << 19 and h.size / 0.9 <= 1 << 20
+    keys = ((h * np.uint64(pow(K, -1, 1 << 32))) & np.uint64(0xFFFFFFFF)).astype(np.uint32).view(np.int32)
+    dim = _dims(rng.permutation(keys), 8)
+    t = _build(dim, 0.9)
+    assert int(t.handle.hash_bits) == 20
+    _check_table(t, dim)
+    assert np.array_equal(_filter_words(t), _bloom_words(dim["key"][dim["flag"] == 1], t.handle.filter_bits // 32))
+
+
 def test_duplicates_are_reported():
     from paper_2607_07632_amd import sdb
     keys = np.random.default_rng(3).permutation(600_000).astype(np.int32) * 7
