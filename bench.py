@@ -541,7 +541,9 @@ def config_record(sdb, name: str, ex, dev, runs: int = 10, balg_rows: int = 16_0
         rec["versus"] = versus
     if ex is not None and name in ("c1_scalar_scan", "c2_join_group"):
         rec["cpu_oracle_one_core"] = one_core_oracle(name, min(n, ONE_CORE_ROWS))
-    if plan.slice_bits:
+    if plan.slice_lds:
+        rec["fused_window_covers"] = "count pass + scatter pass + sums of the table slices in LDS (no fused kernel)"
+    elif plan.slice_bits:
         rec["fused_window_covers"] = "count pass + scatter pass + fused kernel (hash probe over table slices)"
     if any(sdb.dim_info(t)["kind"] == "hash" for t in tabs):
         rec["probes_per_s_run"] = n / (run_ms * 1e-3)

@@ -359,17 +359,19 @@ enum { SDB_LDS_GLOBAL = 0, SDB_LDS_MAP = 1, SDB_LDS_BITS = 2, SDB_LDS_RANK = 3, 
  * rows that can pass the join; the planner takes it when the join's sampled
  * pass fraction, with the filter's false positives added, is at most 0.7
  * (each dropped row saves a scatter write and a probe, each row costs one
- * L2-resident filter read). Where the passing rows of a 2,048th of the table
- * or more fit an LDS table (up to about 8.9M passing rows), the run takes
- * another route when its scratch holds it, as run_scratch_bytes does from 2^24
- * fact rows on:
- * the rows are partitioned so finely (256 to 2,048 slices) that a block sums
- * each slice's rows by dimension row in LDS and only those totals go to their
- * groups; rows that cannot pass find no entry there, so it tests no pass
- * filter. It needs
- * one hash probe, all other stages fact predicates, and the columns those
- * passes read 16-byte aligned. ipt, vector, eager (0), block, grid,
- * lds_bytes and the terminal fields describe that fused launch. */
+ * L2-resident filter read). It needs one hash probe, all other stages fact
+ * predicates, and the columns those passes read 16-byte aligned. ipt, vector,
+ * eager (0), block, grid, lds_bytes and the terminal fields describe that
+ * fused launch.
+ * With slice_lds > 0 as well the rows are partitioned into 2^slice_lds slices,
+ * so many that a block sums each slice's rows by dimension row in LDS, and
+ * only those totals go to their groups; rows that cannot pass find no entry
+ * there, so it tests no pass filter and launches no fused kernel. The planner
+ * takes it from 2^24 fact rows on where the passing rows of a 2,048th of the
+ * table fit an LDS table (up to about 8.9M passing rows), unless the
+ * pre-filter is forced. run_scratch_bytes counts its rows; a run whose scratch
+ * does not hold them takes the route above, which the other fields describe,
+ * if it holds that one's. */
 typedef struct sdb_plan {
     int32_t n_stages;
     int32_t stage_kind[SDB_MAX_STAGES];
@@ -406,6 +408,7 @@ typedef struct sdb_plan {
     int32_t n_parts;
     int32_t part_subs;                    /* PART: record regions per fused-kernel block (1 .. 4): wave
                                              w appends to region w mod part_subs of its block */
+    int32_t slice_lds;                    /* sliced probe: 0, or 2^slice_lds slices summed in LDS (1 .. 11) */
     int64_t part_cap;                     /* PART: records per region */
     int32_t n_group_keys;
     int32_t key_min[SDB_MAX_GROUP_KEYS];

@@ -1125,17 +1125,14 @@ int slice_agg_bits(const sdb_dim* d) {
 struct SliceAggLayout {
     uint64_t hist, part_count, part_start, chunk_start, emit_fill, rec, rec_b, emit, total;
     uint32_t emit_ranges, emit_cap;
-    int bits;
 };
 
 SliceAggLayout slice_agg_layout(const sdb_query* q, const sdb_plan* plan) {
     SliceAggLayout L;
     std::memset(&L, 0, sizeof L);
-    if (plan->slice_bits <= 0) return L;
+    if (plan->slice_bits <= 0 || plan->slice_lds <= 0) return L;
     const sdb_dim* d = q->joins[plan->stage_index[plan->slice_stage]].dim;
-    L.bits = slice_agg_bits(d);
-    if (L.bits == 0) return L;
-    const uint64_t P = 1ull << L.bits, n = (uint64_t)std::max<int64_t>(q->n_fact, 1);
+    const uint64_t P = 1ull << plan->slice_lds, n = (uint64_t)std::max<int64_t>(q->n_fact, 1);
     const uint64_t ranges = (plan->n_groups + (1ull << kSliceEmitShift) - 1) >> kSliceEmitShift;
     if (plan->n_groups > kSliceAggMaxGroups && ranges <= kSliceEmitMaxRanges) {
         // an entry per passing dimension row and work item of its slice, twice
@@ -2046,10 +2043,10 @@ SDB_API sdb_status sdb_plan_star_query(const sdb_query* q, void* scratch, int64_
             plan->slice_prefilter = (q->force_prefilter == 1 || p + (1.0 - p) * fp <= kPrefilterMaxKept) ? 1 : 0;
         }
         plan->run_scratch_bytes += (int64_t)slice_layout(q, plan).total;
-        // the LDS route's rows and records too, from the row count on that the
-        // planner takes slices by itself; a smaller (forced) plan takes that
-        // route when its caller's scratch happens to hold it
-        if (q->n_fact >= kSliceMinRows)
+        // the LDS route, from the row count on that the planner takes slices by
+        // itself (a smaller, forced plan runs through L2), with its rows and records
+        if (q->n_fact >= kSliceMinRows && q->force_prefilter != 1) plan->slice_lds = slice_agg_bits(d);
+        if (plan->slice_lds > 0)
             plan->run_scratch_bytes = std::max(plan->run_scratch_bytes, (int64_t)slice_agg_layout(q, plan).total +
                                                                             (xcd ? (int64_t)copy_bytes : 0));
     }
@@ -2114,6 +2111,10 @@ SDB_API sdb_status sdb_run_star_query(const sdb_query* q, const sdb_plan* plan, 
             plan->slice_grid > kSliceMaxGrid || plan->eager != 0)
             return fail(SDB_INVALID_ARG, "bad sliced-probe plan");
     }
+    if (plan->slice_lds != 0 &&
+        (!sliced || plan->slice_lds < 0 || plan->slice_lds > kSliceMaxBits ||
+         plan->slice_lds > q->joins[plan->stage_index[plan->slice_stage]].dim->hash_bits))
+        return fail(SDB_INVALID_ARG, "bad plan slice_lds %d", plan->slice_lds);
     if (plan->slice_prefilter != 0 &&
         (plan->slice_prefilter != 1 || !sliced ||
          q->joins[plan->stage_index[plan->slice_stage]].dim->filter_kind == SDB_FILTER_NONE))
@@ -2161,12 +2162,10 @@ SDB_API sdb_status sdb_run_star_query(const sdb_query* q, const sdb_plan* plan, 
     }
 
     hipStream_t s = (hipStream_t)stream;
-    // a sliced probe takes its LDS route where the table's slices fit LDS and
-    // the scratch holds that route's rows (as run_scratch_bytes of a plan for at
-    // least kSliceMinRows rows does)
+    // the plan's LDS route, where the scratch holds its rows (run_scratch_bytes does)
     const SliceAggLayout AL = slice_agg_layout(q, plan);
     const uint64_t copy_bytes = plan->xcd_copies ? term_scratch : 0;
-    const bool slice_agg = sliced && AL.bits > 0 && (uint64_t)scratch_bytes >= AL.total + copy_bytes;
+    const bool slice_agg = plan->slice_lds > 0 && (uint64_t)scratch_bytes >= AL.total + copy_bytes;
     uint8_t* slice_base = (uint8_t*)scratch + stage_bytes;
     uint8_t* term_base = slice_base + (slice_agg ? AL.total : SL.total);
     SliceAggParams ap;
@@ -2197,7 +2196,7 @@ SDB_API sdb_status sdb_run_star_query(const sdb_query* q, const sdb_plan* plan, 
     if (slice_agg) {
         // (whole groups of four rows; no other rounding, so that every block has its share)
         sp.rows_per_block = (int64_t)align_up((uint64_t)((q->n_fact + plan->slice_grid - 1) / plan->slice_grid), 4);
-        sp.bits = AL.bits;
+        sp.bits = plan->slice_lds;
         sp.hist = (uint32_t*)(slice_base + AL.hist);
         sp.part_count = (uint32_t*)(slice_base + AL.part_count);
         sp.part_start = (uint32_t*)(slice_base + AL.part_start);
@@ -2206,7 +2205,7 @@ SDB_API sdb_status sdb_run_star_query(const sdb_query* q, const sdb_plan* plan, 
         sp.out_val2 = sp.val2_col >= 0 ? (int32_t*)(slice_base + AL.rec_b) : nullptr;
         sp.item_rows = kSliceAggItem;
         ap.st = p.st[plan->slice_stage];
-        ap.bits = AL.bits;
+        ap.bits = plan->slice_lds;
         ap.agg_kind = q->agg.kind;
         ap.part_start = sp.part_start;
         ap.chunk_start = sp.chunk_start;

@@ -327,11 +327,12 @@ def test_prefilter_agrees_with_the_oracle(n, span):
                   {"slice": 1, "prefilter": 1, "terminal": "part"}, {"slice": 1, "prefilter": -1}):
         got, q = run_gpu(w, force=force)
         assert q.plan_obj.slice_bits > 0 and q.plan_obj.slice_prefilter == (force["prefilter"] == 1)
+        assert q.plan_obj.slice_lds == 0      # through L2: the other route tests no filter
         assert_same(got.as_rows(), want, f"{w.name}, {n} rows, {force}")
     w2 = datagen.Workload(w.name, w.n_fact, w.fact, w.dims, w.dim_keys,
                           {**w.query, "agg": {"kind": "sub", "a": "value", "b": "key"}})
     got, q = run_gpu(w2, force={"slice": 1, "prefilter": 1})
-    assert q.plan_obj.slice_prefilter == 1
+    assert q.plan_obj.slice_prefilter == 1 and q.plan_obj.slice_lds == 0
     assert_same(got.as_rows(), oracle_rows(w2), f"{w.name}, {n} rows, value - key")
 
 
@@ -348,7 +349,7 @@ def test_prefilter_on_random_tiny_schemas(n):
         w = _sliceable(w0, load_factor=(0.5, 0.25, 0.9)[seed % 3], keep_agg=seed % 2 == 1)
         for force in ({"slice": 1, "prefilter": 1}, {"slice": 1, "prefilter": 1, "order": True}):
             got, q = run_gpu(w, force=force)
-            assert q.plan_obj.slice_prefilter == (1 if n else 0), (seed, force)
+            assert q.plan_obj.slice_prefilter == (1 if n else 0) and q.plan_obj.slice_lds == 0, (seed, force)
             assert_same(got.as_rows(), oracle_rows(w), f"seed {seed} n {n} {force}")
         done += 1
         if done == 3:
@@ -362,7 +363,7 @@ def test_c5_prefilter_is_the_planners_choice():
     w = workload("c5_hash_stress")
     want = want_rows("c5_hash_stress")
     got, q = run_gpu(w, force={"slice": 1})
-    assert q.plan_obj.slice_prefilter == 1
+    assert q.plan_obj.slice_prefilter == 1 and q.plan_obj.slice_lds == 0
     from paper_2607_07632_amd import sdb
     assert sdb.plan_summary(q.plan_obj, w.query)["stages"][-1].get("prefilter") is True
     assert_same(got.as_rows(), want, "c5 pre-filtered")

@@ -1,8 +1,8 @@
 """The sliced hash probe's LDS route (rows partitioned by table slice, summed
 by dimension row in LDS) where it can go wrong: slices that overfill the LDS
 table, runs past a slice's end and around the table's, hot keys split over
-work items, every way the groups leave, and a scratch that only holds the
-route through L2. Everything is compared with the oracle, exactly."""
+work items, every way the groups leave, a scratch that only holds the route
+through L2, and that route. Everything is compared with the oracle, exactly."""
 
 import numpy as np
 import pytest
@@ -39,14 +39,23 @@ def _workload(keys, n, seed, attr=None, groups=700, lf=0.5, fact_key=None, preds
                             {"big": "key"}, query)
 
 
-def _check(w, force=None, label="", through_l2=False):
+def _lds_bits(d):
+    """The slices the planner gives a table of this many passing rows."""
+    return next(b for b in range(8, 12) if (d.n_pass >> b) <= 4096 or b == 11)
+
+
+def _check(w, force=None, label="", through_l2=False, bits=None):
     import torch
     from paper_2607_07632_amd import sdb
     require_gpu()
     fact, dims = upload(w)
     q = sdb.StarQuery(fact, sdb.build_dims(dims, w.dim_keys, w.query), w.query, {"slice": 1, **(force or {})})
     plan = q.plan()
-    assert plan.slice_bits > 0
+    # (so few rows run through L2 unless the plan says otherwise)
+    assert plan.slice_bits > 0 and plan.slice_lds == 0
+    if not through_l2:
+        d = q.tables[0].handle
+        plan.slice_lds = min(bits or _lds_bits(d), d.hash_bits)
     sums, counts = q.alloc_outputs()
     # (a plan for so few rows does not count the LDS route's scratch)
     need = int(plan.run_scratch_bytes) + (0 if through_l2 else 128 << 20)
@@ -113,11 +122,39 @@ def test_a_hot_key_over_several_work_items():
 
 @pytest.mark.parametrize("n", [1, 5, 4099, 16_384, 131_075])
 def test_both_routes_at_chunk_edges(n):
-    """The LDS route, and the route through L2 in the plan's own scratch, which
-    is too small for the other's records."""
+    """The LDS route, and the route through L2, which a plan for so few rows takes."""
     keys = np.random.default_rng(13).choice(1 << 31, 3000, replace=False).astype(np.int32)
     w = _workload(keys, n, 14, groups=5000)
     for agg in ("col", "sub"):
         w.query["agg"] = {"kind": agg, "a": "value", "b": None if agg == "col" else "other"}
         for l2 in (False, True):
             _check(w, {"terminal": "global", "xcd": -1}, f"{agg}, {'L2' if l2 else 'LDS'}", l2)
+
+
+def test_the_planners_route_and_a_scratch_that_holds_the_other_alone():
+    """2^24 rows and a table of 2^21 slots: slices summed in LDS; with the
+    pre-filter forced, a plan for the run through L2; and a plan for LDS whose
+    scratch is short of it, but not of the run through L2 that it describes too."""
+    import torch
+    from paper_2607_07632_amd import sdb
+    require_gpu()
+    rng = np.random.default_rng(15)
+    keys = rng.permutation(1 << 20).astype(np.int32)
+    w = _workload(keys, 1 << 24, 15, groups=900)
+    want = oracle_rows(w)
+    fact, dims = upload(w)
+    tables = sdb.build_dims(dims, w.dim_keys, w.query)
+    for force, lds, short in (
+            (None, 8, 0), ({"prefilter": 1}, 0, 0), ({"prefilter": -1}, 8, 0), ({"prefilter": -1}, 8, 65_536)):
+        q = sdb.StarQuery(fact, tables, w.query, force)
+        plan = q.plan()
+        assert plan.slice_bits > 0 and plan.slice_lds == lds
+        st = sdb.plan_summary(plan, w.query)["stages"][plan.slice_stage]
+        assert st["slices_in"] == ("lds" if lds else "l2") and st["table_slices"] == 1 << (lds or plan.slice_bits)
+        sums, counts = q.alloc_outputs()
+        scratch = torch.full((int(plan.run_scratch_bytes) - short,), 0xA5, dtype=torch.uint8, device="cuda")
+        q.run(sums, counts, scratch=scratch)
+        k, s, c, n, _ = q.finalize(sums, counts)
+        m = int(n.item())
+        got = sdb.QueryResult(k[:m].to(torch.int64).cpu().numpy(), s[:m].cpu().numpy(), c[:m].cpu().numpy())
+        assert_same(got.as_rows(), want, f"{force} {lds} {short}")

@@ -352,6 +352,40 @@ def test_sliced_plan_validation():
     assert short == 4                                       # SDB_WORKSPACE_TOO_SMALL
 
 
+def test_slices_in_lds_choice():
+    """Planned from 2^24 rows on, not behind a forced pre-filter, with the
+    scratch its rows need; a plan's value is checked, and too little scratch
+    for it is enough where it holds the route through L2."""
+    def plan(n=600_000_000, force=0, **kw):
+        q, d = _c5_like(n, filt="bitmap", **kw)
+        q.force_prefilter, q.force_slice = force, 1
+        p = sdb.SdbPlan()
+        assert sdb.lib().sdb_plan_star_query(C.byref(q), None, 0, None, C.byref(p)) == OK, sdb.lib().sdb_last_error()
+        check_plan(q, p)
+        return q, d, p
+
+    assert plan()[2].slice_lds == 11
+    assert plan(force=-1)[2].slice_lds == 11
+    assert plan(force=1)[2].slice_lds == 0
+    assert plan(n=(1 << 24) - 1)[2].slice_lds == 0
+    assert plan(n=1 << 24)[2].slice_lds == 11
+    assert plan(pass_frac=0.9)[2].slice_lds == 0          # its slices would overfill LDS
+    q, d, p = plan()
+    for value in (-1, 12, d.hash_bits + 1):
+        bad = sdb.SdbPlan.from_buffer_copy(p)
+        bad.slice_lds = value
+        assert _run_status(q, bad) == INVALID_ARG
+    bad = sdb.SdbPlan.from_buffer_copy(p)
+    bad.slice_bits = 0
+    assert _run_status(q, bad) == INVALID_ARG
+    # 8 bytes a row for the route in LDS beside its records and counts
+    q0, _d0, p0 = plan(force=1)
+    assert p.run_scratch_bytes >= 8 * 600_000_000 + 4 * 256 * 2048
+    if not GPU_PRESENT:
+        p.run_scratch_bytes = p0.run_scratch_bytes
+        assert _run_status(q, p) in (OK, HIP_ERROR), sdb.lib().sdb_last_error()
+
+
 def _bloom_false_positive(bits, n_keys):
     """Blocked Bloom filter, 3 bits of one 32-bit word per key: the chance
     that all 3 bits of a key not in the set are set, a word holding
