@@ -1111,15 +1111,29 @@ SliceLayout slice_layout(const sdb_query* q, const sdb_plan* plan) {
 }
 
 // The LDS route of a sliced probe (slice_agg_kernel): as many partitions as
-// leave at most 8/9 of kSliceAggEntries passing keys to each (2^kSliceAggMinBits at
-// least, where the table has that many slots), or 0 where even the most
-// partitions would overfill the LDS table: then the fused kernel probes the
-// slices through L2.
+// leave at most 8/9 of kSliceAggEntries passing keys to each and at most
+// 2^kSliceAggSlotBits table slots (2^kSliceAggMinBits at least, where the table
+// has that many slots), or 0 where even the most partitions would leave more:
+// then the fused kernel probes the slices through L2.
 int slice_agg_bits(const sdb_dim* d) {
-    int bits = kSliceAggMinBits;
+    int bits = std::max(kSliceAggMinBits, d->hash_bits - kSliceAggSlotBits);
     while (bits < kSliceMaxBits && ((uint64_t)d->n_pass >> bits) > kSliceAggEntries / 9 * 8) ++bits;
-    if (((uint64_t)d->n_pass >> bits) > kSliceAggEntries / 18 * 17) return 0;
+    if (bits > kSliceMaxBits || ((uint64_t)d->n_pass >> bits) > kSliceAggEntries / 18 * 17) return 0;
     return std::min(bits, (int)d->hash_bits);
+}
+
+// Whether the LDS route beats the one through L2 behind the pre-filter, which
+// scatters only the share `kept` of the rows. Where the rows carry one value
+// it does at any share up to 512 slices (40M and 200M rows, 8.4M dimension
+// rows, 1% kept: 319 against 421 and 1,511 against 1,753 us; 10%: 332 against
+// 521 and 1,535 against 2,189), from 1,024 on above 2% (16.8M dimension rows,
+// 200M rows: 1% 1,712 against 1,650, 3% 1,715 against 1,770, 10% 1,735 against
+// 2,124). Records of two values cost it more: 256 slices break even at 10% of
+// 200M rows (2,143 against 2,190) and 3% of 40M (440 against 443), 1,024 at
+// about 13% (200M: 2,690 against 2,600 to 2,748; 40M: 629 against 623 to 664).
+bool slice_lds_pays(const sdb_query* q, int bits, double kept) {
+    if (q->agg.kind == SDB_AGG_COL) return bits < 10 || kept > 0.02;
+    return kept > (bits >= 10 ? 0.13 : q->n_fact >= (1ll << 26) ? 0.10 : 0.04);
 }
 
 struct SliceAggLayout {
@@ -2036,16 +2050,20 @@ SDB_API sdb_status sdb_plan_star_query(const sdb_query* q, void* scratch, int64_
         // each row costs one filter read in the count pass, each dropped row
         // saves its scatter write and its probe
         const sdb_dim* d = q->joins[slice_j].dim;
+        double kept = 1.0;   // share of the rows that the pre-filter would keep
         if (d->filter_kind != SDB_FILTER_NONE && q->force_prefilter != -1) {
             const int ss = plan->slice_stage;
             const double p = plan->sampled_rows > 0 ? plan->stage_pass_alone[ss] : plan->stage_pass[ss];
             const double fp = d->filter_kind == SDB_FILTER_BLOOM ? bloom_false_positive(d->filter_bits, d->n_pass) : 0.0;
-            plan->slice_prefilter = (q->force_prefilter == 1 || p + (1.0 - p) * fp <= kPrefilterMaxKept) ? 1 : 0;
+            kept = p + (1.0 - p) * fp;
+            plan->slice_prefilter = (q->force_prefilter == 1 || kept <= kPrefilterMaxKept) ? 1 : 0;
         }
         plan->run_scratch_bytes += (int64_t)slice_layout(q, plan).total;
         // the LDS route, from the row count on that the planner takes slices by
         // itself (a smaller, forced plan runs through L2), with its rows and records
-        if (q->n_fact >= kSliceMinRows && q->force_prefilter != 1) plan->slice_lds = slice_agg_bits(d);
+        const int lds_bits = slice_agg_bits(d);
+        if (q->n_fact >= kSliceMinRows && q->force_prefilter != 1 && slice_lds_pays(q, lds_bits, kept))
+            plan->slice_lds = lds_bits;
         if (plan->slice_lds > 0)
             plan->run_scratch_bytes = std::max(plan->run_scratch_bytes, (int64_t)slice_agg_layout(q, plan).total +
                                                                             (xcd ? (int64_t)copy_bytes : 0));

@@ -158,3 +158,31 @@ def test_the_planners_route_and_a_scratch_that_holds_the_other_alone():
         m = int(n.item())
         got = sdb.QueryResult(k[:m].to(torch.int64).cpu().numpy(), s[:m].cpu().numpy(), c[:m].cpu().numpy())
         assert_same(got.as_rows(), want, f"{force} {lds} {short}")
+
+
+@pytest.mark.parametrize("agg,lds", [("col", 9), ("sub", 9)])
+def test_a_large_table_few_of_whose_rows_pass(agg, lds):
+    """2^23 dimension rows in 2^24 slots, a tenth passing: 512 slices of 2^15
+    slots, whose runs' slot numbers stay below 2^16 (256 slices would hold the
+    passing rows, but not the slots)."""
+    import torch
+    from paper_2607_07632_amd import sdb
+    require_gpu()
+    rng = np.random.default_rng(16)
+    keys = rng.permutation(1 << 23).astype(np.int32)
+    w = _workload(keys, (1 << 24) + 3, 16, groups=3000, agg=agg)
+    w.dims["big"]["flag"][:] = rng.integers(0, 10, keys.size) == 1
+    fact, dims = upload(w)
+    q = sdb.StarQuery(fact, sdb.build_dims(dims, w.dim_keys, w.query), w.query)
+    plan = q.plan()
+    assert plan.slice_lds == lds and q.tables[0].handle.hash_bits == 24
+    assert_same(q.execute().as_rows(), oracle_rows(w), agg)
+    if agg == "col":     # and in several rounds a slice, which a plan may still ask for
+        plan = q.plan_obj
+        plan.slice_lds = 8
+        sums, counts = q.alloc_outputs()
+        q.run(sums, counts, scratch=torch.empty(int(plan.run_scratch_bytes) + (64 << 20), dtype=torch.uint8, device="cuda"))
+        again = q.alloc_outputs()
+        plan.slice_lds = lds
+        q.run(*again)
+        assert bool((sums == again[0]).all()) and bool((counts == again[1]).all())

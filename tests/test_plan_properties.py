@@ -386,6 +386,34 @@ def test_slices_in_lds_choice():
         assert _run_status(q, p) in (OK, HIP_ERROR), sdb.lib().sdb_last_error()
 
 
+@pytest.mark.parametrize("hash_bits,pass_frac,filt,agg,n,want", [
+    (24, 0.12, "bitmap", 0, 1 << 24, 9),      # slices by slots: 256 of them would hold 65,536 slots and more
+    (24, 0.01, "bitmap", 0, 200_000_000, 9),
+    (25, 0.06, "bitmap", 0, 40_000_000, 10),
+    (25, 0.01, "bitmap", 0, 40_000_000, 0),   # 1,024 slices and one row in a hundred kept: through L2
+    (25, 0.01, None, 0, 40_000_000, 10),      # ... but nothing to keep them by
+    (26, 0.05, "bitmap", 0, 40_000_000, 11),
+    (27, 0.03, "bloom", 0, 40_000_000, 0),   # 2^16 slots a slice at the most slices
+    (31, 0.001, "bloom", 0, 40_000_000, 0),
+    (21, 0.01, "bitmap", 0, 40_000_000, 8),
+    (21, 0.03, "bitmap", 2, 40_000_000, 0),   # two values a row
+    (21, 0.05, "bitmap", 2, 40_000_000, 8),
+    (21, 0.09, "bitmap", 2, 200_000_000, 0),
+    (24, 0.11, "bitmap", 2, 200_000_000, 9),
+    (25, 0.12, "bitmap", 2, 40_000_000, 0),
+    (25, 0.14, "bitmap", 2, 40_000_000, 10),
+])
+def test_slices_in_lds_by_slots_and_kept_rows(hash_bits, pass_frac, filt, agg, n, want):
+    """A slice of the LDS route has at most 2^15 slots (its slot numbers have 16
+    bits), and the route is taken where it beats the pre-filtered one."""
+    q, d = _c5_like(n, hash_bits, filt=filt, pass_frac=pass_frac, agg_kind=agg)
+    p = sdb.SdbPlan()
+    assert sdb.lib().sdb_plan_star_query(C.byref(q), None, 0, None, C.byref(p)) == OK, sdb.lib().sdb_last_error()
+    check_plan(q, p)
+    assert p.slice_bits and p.slice_lds == want
+    assert want == 0 or (d.n_slots >> want <= 1 << 15 and d.n_pass >> want <= 4608)
+
+
 def _bloom_false_positive(bits, n_keys):
     """Blocked Bloom filter, 3 bits of one 32-bit word per key: the chance
     that all 3 bits of a key not in the set are set, a word holding
