@@ -419,13 +419,71 @@ sdb_status check_query(const sdb_query* q) {
     return SDB_OK;
 }
 
-// Whether a stage probes a hash table.
-bool probes_hash(const sdb_query* q, const sdb_plan* plan) {
+// The hash table stage s probes, or null.
+const sdb_dim* probed_table(const sdb_query* q, const sdb_plan* plan, int s) {
+    if (plan->stage_kind[s] != 1 || plan->stage_range[s]) return nullptr;
+    const sdb_dim* d = q->joins[plan->stage_index[s]].dim;
+    return d->kind != SDB_TABLE_DENSE ? d : nullptr;
+}
+
+// Whether a stage probes a hash table, and the largest one probed.
+const sdb_dim* largest_probed(const sdb_query* q, const sdb_plan* plan) {
+    const sdb_dim* most = nullptr;
+    for (int s = 0; s < plan->n_stages; ++s) {
+        const sdb_dim* d = probed_table(q, plan, s);
+        if (d && (!most || d->n_slots > most->n_slots)) most = d;
+    }
+    return most;
+}
+bool probes_hash(const sdb_query* q, const sdb_plan* plan) { return largest_probed(q, plan) != nullptr; }
+
+// Whether the fused kernel tests a hash stage's pass filter before the probe:
+// for a table larger than an XCD's L2 where the filter keeps few enough rows.
+// A filter read costs half a probe of 8 MiB, a third of one of 16 or 32 MiB and
+// again half of one whose filter (8 bits a row, at most 4 MiB) takes up the
+// L2, where another hash table's slots compete with it. Measured with the
+// filter and without, one join of 16M rows and two of 30M, in us:
+//   8 MiB   50% kept  194, 215 and 502, 540;  60%  209, 212 and 552, 558;  65%  218, 216 and 580, 569
+//   16 MiB  60%       223, 262 and 607, 670;  65%  234, 263 and 640, 679
+//   32 MiB  60%       266, 298 and 796, 795;  65%  284, 298 and 848, 806
+//   64 MiB  50%       308, 327 and 870, 843;  55%  327, 327 and 933, 864
+//   128 MiB 50%       319, 343 and 900, 905;  55%  340, 342 and 964, 928
+bool probe_filter(const sdb_query* q, const sdb_plan* plan, int s) {
+    const sdb_dim* d = probed_table(q, plan, s);
+    if (!d || d->filter_kind == SDB_FILTER_NONE || q->force_prefilter == -1) return false;
+    const uint64_t bytes = d->n_slots * 8u;
+    if (bytes <= (4ull << 20)) return false;
+    int tables = 0;
+    for (int i = 0; i < plan->n_stages; ++i) tables += probed_table(q, plan, i) ? 1 : 0;
+    const double line = bytes <= (8ull << 20)    ? 0.58
+                        : bytes <= (32ull << 20) ? (tables == 1 ? 0.67 : 0.62)
+                                                 : (tables == 1 ? 0.56 : 0.50);
+    const double p = plan->stage_pass_alone[s];
+    const double fp = d->filter_kind == SDB_FILTER_BLOOM ? bloom_false_positive(d->filter_bits, d->n_pass) : 0.0;
+    return p + (1.0 - p) * fp <= line;
+}
+
+// Whether a plan with a hash probe runs the instances whose rows go through
+// their chains together, two slots a turn (stage_probe), and not row by row,
+// one slot at a time (stage_hash). Together pays where a turn's latency is
+// long or many rows need a second one, row by row where the requests count:
+// in tables around the L2's size, whose second slots miss it, in sparse ones,
+// and in nearly full ones, where one row's chain holds up the others'. From
+// row by row to together, one join of 12M rows: 2 MiB 0.32 full 105.6 -> 105.9
+// us, 0.5 138.5 -> 137.0; 4 MiB 0.5 148.1 -> 151.8 (30M rows 330 -> 348), 0.6
+// 183.9 -> 178.7; 16 MiB 0.32 191.4 -> 187.4, 0.5 210.7 -> 201.9, 0.88 901 ->
+// 961; 64 MiB 0.5 265.2 -> 249.5. Over table slices of 2 MiB, 150M rows: 2^25
+// slots 0.3 full 3,256 -> 3,098, 0.5 3,820 -> 3,317, 0.88 13,407 -> 10,383;
+// 2^26 slots 0.26 3,450 -> 3,535, 0.34 3,602 -> 3,573.
+bool probes_together(const sdb_query* q, const sdb_plan* plan) {
+    const sdb_dim* d = largest_probed(q, plan);
+    const double load = (double)d->n_rows / (double)d->n_slots;
+    if (plan->slice_bits != 0) return load > 1.0 / 3.0 || d->n_slots < (1ull << 26);
     for (int s = 0; s < plan->n_stages; ++s)
-        if (plan->stage_kind[s] == 1 && !plan->stage_range[s] &&
-            q->joins[plan->stage_index[s]].dim->kind != SDB_TABLE_DENSE)
-            return true;
-    return false;
+        if (probe_filter(q, plan, s)) return true;
+    if (load > 0.8) return false;
+    const uint64_t bytes = d->n_slots * 8u;
+    return bytes >= (16ull << 20) || load >= (bytes <= (2ull << 20) ? 0.42 : 0.55);
 }
 
 // Whether the fused kernel runs 4-row items: on 16-byte aligned columns
@@ -455,9 +513,10 @@ bool unroll_allowed(const sdb_query* q, const sdb_plan* plan) {
 
 // The instance a run takes: the plan's choice, and for 4-row items on
 // unaligned columns (plan->vector and so plan->unroll 0) the same rule.
-// -1: the instance for plans with a hash probe (unless its shape is forced otherwise).
+// -1: the instance for hash probes whose rows go on together.
 int run_unroll(const sdb_query* q, const sdb_plan* plan) {
-    if (plan->vector && plan->ipt <= 2 && plan->eager == 0 && probes_hash(q, plan)) return -1;
+    if (plan->vector && plan->ipt <= 2 && plan->eager == 0 && probes_hash(q, plan) && probes_together(q, plan))
+        return -1;
     if (plan->vector) return plan->unroll;
     return q->force_unroll != -1 && unroll_allowed(q, plan) ? 1 : 0;
 }
@@ -1032,23 +1091,6 @@ constexpr int kSliceLog2Bytes = 21;
 // saves.
 constexpr double kPrefilterMaxKept = 0.7;
 
-// Whether the fused kernel tests a hash stage's pass filter before the probe:
-// for a table larger than an XCD's L2 whose filter drops enough rows (the
-// sliced probe's line, since a filter read costs about a quarter of a probe).
-// Measured: two joins of 24M rows, 29% passing the 8 MB table: 369 -> 329 us;
-// of 60M rows with a table of 32 MB 1,216 -> 834.
-constexpr uint64_t kProbeFilterMinTableBytes = 4ull << 20;
-
-bool probe_filter(const sdb_query* q, const sdb_plan* plan, int s) {
-    if (plan->stage_kind[s] != 1 || plan->stage_range[s] || q->force_prefilter == -1) return false;
-    const sdb_dim* d = q->joins[plan->stage_index[s]].dim;
-    if (d->kind != SDB_TABLE_HASH || d->filter_kind == SDB_FILTER_NONE || d->n_slots * 8u <= kProbeFilterMinTableBytes)
-        return false;
-    const double p = plan->stage_pass_alone[s];
-    const double fp = d->filter_kind == SDB_FILTER_BLOOM ? bloom_false_positive(d->filter_bits, d->n_pass) : 0.0;
-    return p + (1.0 - p) * fp <= kPrefilterMaxKept;
-}
-
 // The join the query allows to run over table slices, or -1: the only join,
 // into a hash table, with every other stage a fact predicate, a SUM of one
 // column (the partitioned records carry one 32-bit value), and the columns
@@ -1203,7 +1245,8 @@ uint32_t launch_lds_bytes(const sdb_query* q, const sdb_plan* plan) {
 // LDS a block may use so that the blocks the grid counts on all fit (see choose_grid).
 constexpr uint32_t kLdsUsable = 152u * 1024u;
 
-sdb_status choose_grid(const sdb_query* q, const sdb_plan* plan, int* grid_out) {
+// `unroll`: run_unroll of the plan.
+sdb_status choose_grid(const sdb_query* q, const sdb_plan* plan, int unroll, int* grid_out) {
     const int wide = wide_items(q, plan) ? 1 : 0;
     const int64_t rows_per_item = wide ? 4 : 1;
     const int64_t n_items = q->n_fact / rows_per_item;
@@ -1217,7 +1260,7 @@ sdb_status choose_grid(const sdb_query* q, const sdb_plan* plan, int* grid_out) 
     DeviceInfo di;
     sdb_status st = device_info(&di);
     if (st != SDB_OK) return st;
-    int per_cu = fused_blocks_per_cu(wide, plan->ipt, plan->terminal, plan->eager, plan->block, run_unroll(q, plan),
+    int per_cu = fused_blocks_per_cu(wide, plan->ipt, plan->terminal, plan->eager, plan->block, unroll,
                                      (size_t)launch_lds_bytes(q, plan));
     if (per_cu <= 0) return fail(SDB_HIP_ERROR, "occupancy query failed for the fused kernel");
     // The occupancy query counts LDS as if all 160 KB were available in fine
@@ -2005,7 +2048,7 @@ SDB_API sdb_status sdb_plan_star_query(const sdb_query* q, void* scratch, int64_
         // records are written per block: the grid is fixed now
         if (plan->grid <= 0) {
             int grid = 0;
-            st = choose_grid(q, plan, &grid);
+            st = choose_grid(q, plan, run_unroll(q, plan), &grid);
             if (st != SDB_OK) return st;
             plan->grid = grid;
         }
@@ -2168,8 +2211,9 @@ SDB_API sdb_status sdb_run_star_query(const sdb_query* q, const sdb_plan* plan, 
     const uint32_t lds_bytes = launch_lds_bytes(q, plan);
     if (lds_bytes > 160u * 1024u) return fail(SDB_UNSUPPORTED, "plan needs %u bytes of LDS", lds_bytes);
     p.ring_off = (uint32_t)plan->lds_bytes;
+    const int unroll = run_unroll(q, plan);
     // (a sliced probe has its own pre-filter)
-    for (int st_i = 0; !sliced && run_unroll(q, plan) < 0 && st_i < plan->n_stages; ++st_i) {
+    for (int st_i = 0; !sliced && unroll < 0 && st_i < plan->n_stages; ++st_i) {
         if (!probe_filter(q, plan, st_i)) continue;
         const sdb_dim* fd = q->joins[plan->stage_index[st_i]].dim;
         p.st[st_i].op = OP_HASH_FILTER;
@@ -2387,7 +2431,7 @@ SDB_API sdb_status sdb_run_star_query(const sdb_query* q, const sdb_plan* plan, 
     } else if (q->n_fact > 0) {
         int grid = plan->grid;
         if (grid <= 0) {
-            st = choose_grid(q, plan, &grid);
+            st = choose_grid(q, plan, unroll, &grid);
             if (st != SDB_OK) return st;
         }
         const bool timed = g_fused_start && g_fused_stop;
@@ -2410,7 +2454,7 @@ SDB_API sdb_status sdb_run_star_query(const sdb_query* q, const sdb_plan* plan, 
                 }
                 pg.region_base = (uint32_t)((uint64_t)g * (uint64_t)grid);
             }
-            SDB_HIP(launch_fused(pg, wide_items(q, plan), plan->ipt, plan->terminal, plan->eager, run_unroll(q, plan), grid,
+            SDB_HIP(launch_fused(pg, wide_items(q, plan), plan->ipt, plan->terminal, plan->eager, unroll, grid,
                                  plan->block, lds_bytes, s),
                     "fused kernel launch");
         }

@@ -360,74 +360,67 @@ __device__ __forceinline__ void stage_filter(const StageDev& S, const int32_t (&
     SDB_ROWS(j, r) al[j][r] = al[j][r] && (w[j][r] & m[j][r]) == m[j][r];
 }
 
-// The hash probe of the instances for plans that make one (UNR < 0; the others
-// keep stage_hash, which they reach only when their shape is forced: this one's
-// code in them slowed plans without a hash table: c3's shape 2.17 -> 2.42 ms). An item's rows go on together, two slots a turn, until none of the wave's is
-// left, so a turn costs one table latency for all of them (150M rows through
-// L2 slices: 2.41 -> 1.94 ms). Where the host asks for it, a row first tests the
-// table's pass filter, a read that hits L2 where the probe would not:
-// a probe of a table past L2 runs at about 54G rows/s, a filter read at 215G.
+// The hash probe of the instances with UNR < 0, which the host chooses for
+// 4-row items on aligned columns by the tables' size and load (sdb_api.cpp,
+// probes_together); the other instances, 1-row items on unaligned columns among
+// them, keep stage_hash. (This one's code in them slowed plans without a hash
+// table: c3's shape 2.17 -> 2.42 ms.) An item's four rows go on together, two
+// slots a turn, until none of the wave's is left, so a turn costs one table
+// latency for all of them (150M rows through L2 slices: 2.41 -> 1.94 ms). Where
+// the host asks for it, the rows first test the table's pass filter
+// (stage_filter).
 template <int W, int IPT, bool PAIR>
 __device__ __forceinline__ void stage_probe(const StageDev& S, const int32_t (&x)[IPT][W], bool (&al)[IPT][W],
                                            uint32_t (&gid)[IPT][W]) {
     const unsigned long long* tab = static_cast<const unsigned long long*>(S.map);
-    constexpr int HJ = 1;
 #pragma unroll
-    for (int j0 = 0; j0 < IPT; j0 += HJ) {
-        uint32_t h[HJ][W], c[HJ][W];
-        bool pend[HJ][W];
+    for (int j = 0; j < IPT; ++j) {
+        uint32_t h[W], c[W];
+        bool pend[W];
 #pragma unroll
-        for (int jj = 0; jj < HJ; ++jj)
+        for (int r = 0; r < W; ++r) {
+            h[r] = hash_slot(S, x[j][r]);
+            c[r] = S.sentinel;
+            pend[r] = al[j][r];
+        }
+        for (uint32_t it = 0; it < S.nslots; it += 2u) {   // (a table has an empty slot, which ends every chain)
+            unsigned long long sl[W], sn[W];
 #pragma unroll
             for (int r = 0; r < W; ++r) {
-                h[jj][r] = hash_slot(S, x[j0 + jj][r]);
-                c[jj][r] = S.sentinel;
-                pend[jj][r] = al[j0 + jj][r];
-            }
-        for (uint32_t it = 0; it < S.nslots; it += 2u) {   // (a table has an empty slot, which ends every chain)
-            unsigned long long sl[HJ][W], sn[HJ][W];
-#pragma unroll
-            for (int jj = 0; jj < HJ; ++jj)
-#pragma unroll
-                for (int r = 0; r < W; ++r) {
-                    sl[jj][r] = 0ull;
-                    sn[jj][r] = 0ull;
-                    if (pend[jj][r]) {
-                        // a slot and the next one (mostly the same cache line)
-                        if (PAIR && h[jj][r] != S.hmask) {
-                            const u64x2 pr = *reinterpret_cast<const u64x2_a8*>(tab + h[jj][r]);
-                            sl[jj][r] = pr.x;
-                            sn[jj][r] = pr.y;
-                        } else {
-                            sl[jj][r] = tab[h[jj][r]];
-                            sn[jj][r] = tab[(h[jj][r] + 1u) & S.hmask];
-                        }
+                sl[r] = 0ull;
+                sn[r] = 0ull;
+                if (pend[r]) {
+                    // a slot and the next one (mostly the same cache line)
+                    if (PAIR && h[r] != S.hmask) {
+                        const u64x2 pr = *reinterpret_cast<const u64x2_a8*>(tab + h[r]);
+                        sl[r] = pr.x;
+                        sn[r] = pr.y;
+                    } else {
+                        sl[r] = tab[h[r]];
+                        sn[r] = tab[(h[r] + 1u) & S.hmask];
                     }
                 }
+            }
             bool more = false;
 #pragma unroll
-            for (int jj = 0; jj < HJ; ++jj)
-#pragma unroll
-                for (int r = 0; r < W; ++r) {
-                    const uint32_t k = (uint32_t)x[j0 + jj][r];
-                    const uint32_t e0 = (uint32_t)(sl[jj][r] >> 32), e1 = (uint32_t)(sn[jj][r] >> 32);
-                    const bool hit0 = e0 != 0u && (uint32_t)sl[jj][r] == k;
-                    const bool hit1 = e0 != 0u && e1 != 0u && (uint32_t)sn[jj][r] == k;
-                    if (pend[jj][r] && (hit0 || hit1)) c[jj][r] = (hit0 ? e0 : e1) - 1u;   // a filtered row: the sentinel
-                    pend[jj][r] = pend[jj][r] && e0 != 0u && e1 != 0u && !hit0 && !hit1;
-                    h[jj][r] = (h[jj][r] + 2u) & S.hmask;
-                    more = more || pend[jj][r];
-                }
+            for (int r = 0; r < W; ++r) {
+                const uint32_t k = (uint32_t)x[j][r];
+                const uint32_t e0 = (uint32_t)(sl[r] >> 32), e1 = (uint32_t)(sn[r] >> 32);
+                const bool hit0 = e0 != 0u && (uint32_t)sl[r] == k;
+                const bool hit1 = e0 != 0u && e1 != 0u && (uint32_t)sn[r] == k;
+                if (pend[r] && (hit0 || hit1)) c[r] = (hit0 ? e0 : e1) - 1u;   // a filtered row: the sentinel
+                pend[r] = pend[r] && e0 != 0u && e1 != 0u && !hit0 && !hit1;
+                h[r] = (h[r] + 2u) & S.hmask;
+                more = more || pend[r];
+            }
             if (!__any(more)) break;
         }
 #pragma unroll
-        for (int jj = 0; jj < HJ; ++jj)
-#pragma unroll
-            for (int r = 0; r < W; ++r) {
-                al[j0 + jj][r] = al[j0 + jj][r] && c[jj][r] < S.sentinel;
-                if (S.gk_mode == GK_ONE) gid[j0 + jj][r] += c[jj][r] * S.gk_stride[0];
-                else if (S.gk_mode == GK_GENERAL) gid[j0 + jj][r] += code_contribution(S, c[jj][r]);
-            }
+        for (int r = 0; r < W; ++r) {
+            al[j][r] = al[j][r] && c[r] < S.sentinel;
+            if (S.gk_mode == GK_ONE) gid[j][r] += c[r] * S.gk_stride[0];
+            else if (S.gk_mode == GK_GENERAL) gid[j][r] += code_contribution(S, c[r]);
+        }
     }
 }
 
@@ -740,7 +733,7 @@ const void* pick_fused_vec(int ipt, int terminal);
 const void* pick_fused_big(int ipt, int terminal);
 // 4-row items with eager column loads, ipt 1 or 2, launch bound kMaxBlock;
 const void* pick_fused_eager(int ipt, int terminal);
-// 4-row items for plans with a hash probe (UNR < 0), ipt 1 or 2, blocks of up to kBigBlock;
+// 4-row items for hash probes whose rows go on together (UNR < 0), ipt 1 or 2, blocks of up to kBigBlock;
 const void* pick_fused_probe(int ipt, int terminal);
 // 1-row items, ipt 1, 2 or 4, launch bound kMaxBlock.
 const void* pick_fused_rows(int ipt, int terminal);

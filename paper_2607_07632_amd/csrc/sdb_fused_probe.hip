@@ -1,4 +1,5 @@
-// Instances of the fused pass for plans with a hash probe: 4-row items in blocks of up to kBigBlock threads.
+// Instances of the fused pass for hash probes whose rows go on together (stage_probe): 4-row items in blocks of up to
+// kBigBlock threads.
 
 #include "sdb_fused.h"
 

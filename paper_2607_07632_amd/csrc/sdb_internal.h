@@ -56,7 +56,7 @@ enum StageOp : int32_t {
     OP_WINDOW1 = 17,    // pass bitmap of a key window in LDS, the device map outside it, 1/2/4-byte codes
     OP_WINDOW2 = 18,
     OP_WINDOW4 = 19,
-    OP_HASH_FILTER = 20  // OP_HASH behind the table's pass filter (instances for plans with a hash probe)
+    OP_HASH_FILTER = 20  // OP_HASH behind the table's pass filter (instances with UNR < 0)
 };
 // How a table's code becomes part of the group id.
 enum GroupMode : int32_t { GK_NONE = 0, GK_ONE = 1, GK_GENERAL = 2 };
@@ -450,8 +450,8 @@ hipError_t launch_sample(const FusedParams& p, int64_t step, int64_t n_sample, i
 // the instance does not exist.
 // `unroll`: the instance whose stage loop is written out kUnrollStages times
 // (plans of at most that many stages, 4-row items, 2 per lane, blocks of
-// kMaxBlock or kBigBlock, no eager loads); < 0: the one for plans with a hash
-// probe (4-row items, 1 or 2 per lane, no eager loads).
+// kMaxBlock or kBigBlock, no eager loads); < 0: the one for hash probes whose
+// rows go on together (4-row items, 1 or 2 per lane, no eager loads).
 int fused_blocks_per_cu(int vector, int ipt, int terminal, int eager, int block, int unroll, size_t lds_bytes);
 hipError_t launch_fused(const FusedParams& p, int vector, int ipt, int terminal, int eager, int unroll, int grid,
                         int block, size_t lds_bytes, hipStream_t s);

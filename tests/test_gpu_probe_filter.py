@@ -1,6 +1,7 @@
-"""Hash probes behind the table's pass filter in the fused pass (tables larger
-than an XCD's L2, most rows not passing), at row counts that leave 0 to 3 rows
-past the last whole item: the oracle's groups, with the filter and without."""
+"""Hash probes of the fused pass at row counts that leave 0 to 3 rows past the
+last whole item: behind the table's pass filter (tables larger than an XCD's L2,
+most rows not passing) and without it, rows that go through their chains
+together and row by row. The oracle's groups each time."""
 
 import numpy as np
 import pytest
@@ -33,3 +34,27 @@ def test_filtered_probe(span):
         for force in (None, {"prefilter": -1}, {"ipt": 2}, {"terminal": "global"}, {"terminal": "part"}):
             got, _ = run_gpu(w, force=force, dev=dev)
             assert_same(got.as_rows(), want, f"{span} {n} {force}")
+
+
+@pytest.mark.parametrize("m,lf", [(60_000, 0.5), (40_000, 0.5), (120_000, 0.9), (500_000, 0.5), (300_000, 0.5),
+                                  (600_000, 0.9), (1_100_000, 0.5), (1_900_000, 0.9)])
+def test_tables_of_every_size_and_load(m, lf):
+    """Up to 2 MiB, 4 and 8 MiB, 16 and more, from a quarter to nearly full:
+    where the rows go on together and where row by row, most rows passing."""
+    require_gpu()
+    rng = np.random.default_rng(m)
+    keys = rng.choice(1 << 32, m, replace=False).astype(np.uint32).view(np.int32)
+    dims = {"big": {"k": keys, "f": rng.integers(0, 4, m, dtype=np.int32), "a": rng.integers(0, 50, m, dtype=np.int32)}}
+    n = 150_003
+    miss = rng.integers(-(1 << 31), 1 << 31, n).astype(np.int32)
+    fact = {"k": np.where(rng.random(n) < 0.9, keys[rng.integers(0, m, n)], miss).astype(np.int32),
+            "v": rng.integers(-10**9, 10**9, n, dtype=np.int32)}
+    w = datagen.Workload(f"{m} rows", n, fact, dims, {"big": "k"},
+                         {"fact_preds": [], "joins": [{"fact_key": "k", "dim": "big", "payloads": ["a"], "kind": "hash",
+                                                       "preds": [{"col": "f", "op": "ge", "lo": 1, "hi": None}],
+                                                       "load_factor": lf}],
+                          "group_by": [["big", "a"]], "agg": {"kind": "col", "a": "v", "b": None}})
+    want, dev = oracle_rows(w), upload(w)
+    for force in (None, {"ipt": 2}, {"terminal": "global"}, {"slice": 1}):
+        got, _ = run_gpu(w, force=force, dev=dev)
+        assert_same(got.as_rows(), want, f"{m} {lf} {force}")
