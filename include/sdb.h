@@ -474,9 +474,10 @@ SDB_API sdb_status sdb_struct_sizes(int64_t* sizes, int32_t n);
  * a HASH table of next_pow2(n_rows / load_factor) 8-byte slots, padded to
  * 256 bytes, and its pass filter of min(max(next_pow2(n_rows), 256),
  * SDB_MAX_FILTER_BYTES) bytes). A workspace with 9 bytes a row and 4 MiB more
- * lets a hash table of 2^19 rows or more (at most 2^25 slots) be built slice
- * by slice: its rows partitioned there by table slice, each slice built in
- * LDS and written whole, instead of inserts all over the table. */
+ * lets a hash table of 786,432 rows or more (524,288 where a quarter of them or
+ * more go into a Bloom filter; at most 2^25 slots) be built slice by slice: its
+ * rows partitioned there by table slice, each slice built in LDS and written
+ * whole, instead of inserts all over the table. */
 SDB_API sdb_status sdb_dim_required_bytes(const sdb_dim_desc* desc, int64_t* bytes);
 
 /* Builds the lookup table for `desc` into `workspace` (device, 256-byte

@@ -286,11 +286,12 @@ uint64_t required_bytes(const sdb_dim_desc* d) {
 
 // The sliced build of a hash table of 2^hash_bits slots in the workspace past
 // what sdb_dim_required_bytes counts: true, with the parameters filled, where
-// the table is of its sizes and that room suffices.
-bool hash_slices(const sdb_dim_desc* desc, const BuildParams& bp, int hash_bits, uint8_t* workspace,
+// the table is of its sizes (kHashSliceMinRows says why) and that room suffices.
+bool hash_slices(const sdb_dim_desc* desc, const BuildParams& bp, int64_t n_pass, int hash_bits, uint8_t* workspace,
                  uint64_t workspace_bytes, HashSliceParams* hp) {
     const uint64_t n = (uint64_t)desc->n_rows;
-    if (desc->n_rows < kHashSliceMinRows) return false;
+    const bool atomics = bp.filt && !bp.filt_via_bytes && n_pass >= desc->n_rows / 4;
+    if (desc->n_rows < (atomics ? kHashSliceMinBloomRows : kHashSliceMinRows)) return false;
     const int bits = std::max(hash_bits - kHashSliceSlotBits, std::min(8, hash_bits));
     if (bits > kSliceMaxBits) return false;
     const uint64_t P = 1ull << bits;
@@ -1634,7 +1635,8 @@ SDB_API sdb_status sdb_build_dims(int32_t n_dims, const sdb_dim_desc* descs, voi
             // there; the slots are filled afterwards, the filter by the packing
             bp[d].filt_via_bytes = bitmap && align_up(range, 32) <= slot_bytes ? 1 : 0;
             bp[d].fill_words = (slot_bytes + (bp[d].filt_via_bytes ? 0 : fbytes)) / 4;
-            if (hash_slices(desc, bp[d], bits, (uint8_t*)workspaces[d], (uint64_t)workspace_bytes[d], &slices[d])) {
+            if (hash_slices(desc, bp[d], out->n_pass, bits, (uint8_t*)workspaces[d], (uint64_t)workspace_bytes[d],
+                            &slices[d])) {
                 bp[d].sliced = 1;
                 bp[d].fill_words = 0;   // every slot is written by its slice
             }

@@ -287,12 +287,16 @@ struct BuildParams {
 };
 
 // Sliced build of a hash table (hash_slice_kernel): rows partitioned by table
-// slice, each slice built in LDS. Tables of kHashSliceMinRows rows or more
-// (a step with a table of 530K rows takes 157 us by inserts and 155 by slices,
-// of 1M rows 238 and 181) and at most 2^25 slots, where the workspace has room
-// for the records.
+// slice, each slice built in LDS. Tables of kHashSliceMinRows rows or more and
+// at most 2^25 slots, where the workspace has room for the records; from
+// kHashSliceMinBloomRows on where a quarter of the rows or more go into a Bloom
+// filter, whose atomics slow the inserts. Built by inserts and by slices, half
+// full: 530K rows 75 and 81 us (bitmap), 72 and 78 (Bloom, 2% passing), 104 and
+// 85 (Bloom, half passing); 700K 82 and 82, 83 and 80, 124 and 90; 786K 87 and
+// 83, 93 and 85, 141 and 95; 1.05M 101 and 91, 120 and 98, 184 and 110.
 constexpr int kHashSliceSlotBits = 14;          // at most 2^14 slots a slice (128 KB of LDS)
-constexpr int64_t kHashSliceMinRows = 1ll << 19;
+constexpr int64_t kHashSliceMinRows = 3ll << 18;
+constexpr int64_t kHashSliceMinBloomRows = 1ll << 19;
 constexpr int kHashSliceGrid = 256;             // blocks of its count and scatter passes
 constexpr uint32_t kHashSliceRetry = 8u;        // DimStats.dup: too uneven for slices, build with inserts
 

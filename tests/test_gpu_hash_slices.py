@@ -1,4 +1,4 @@
-"""Hash tables built slice by slice (2^19 rows or more): every row is found
+"""Hash tables built slice by slice (786,432 rows or more, with a Bloom filter 2^19): every row is found
 where linear probing looks for it, the pass filter is as documented, and
 duplicates and uneven hashes are met as by inserts."""
 
@@ -65,28 +65,43 @@ def _check_table(t, dim):
     assert np.array_equal(full[home.astype(np.int64) + dist] - full[home.astype(np.int64)], dist)
 
 
-@pytest.mark.parametrize("m,lf", [((1 << 19) - 1, 0.5), (1 << 19, 0.5), (700_001, 0.9), (1_300_003, 0.3)])
-def test_slots_and_filter(m, lf):
-    keys = np.random.default_rng(m).choice(1 << 32, m, replace=False).astype(np.uint32).view(np.int32)
+def _was_sliced(t, m):
+    """Whether the build wrote its records into the workspace past the required
+    bytes: their middle, 9 bytes a row and 4 MiB before the end."""
+    at = t.workspace.numel() - (9 * m + (4 << 20)) + (1 << 20) + 4 * m
+    return bool((t.workspace[at:at + 4096] != 0xA5).any())
+
+
+@pytest.mark.parametrize("m,lf,eighths,sliced", [
+    ((1 << 19) - 1, 0.5, 4, False), (1 << 19, 0.5, 4, True), ((3 << 18) - 1, 0.5, 1, False), (3 << 18, 0.5, 1, True),
+    (700_001, 0.9, 4, True), (1_300_003, 0.3, 4, True)])
+def test_slots_and_filter(m, lf, eighths, sliced):
+    """The smallest tables built by slices, and the largest that are not: half
+    of the rows or one in eight in the Bloom filter."""
+    rng = np.random.default_rng(m)
+    keys = rng.choice(1 << 32, m, replace=False).astype(np.uint32).view(np.int32)
     dim = _dims(keys, m)
+    dim["flag"] = (rng.integers(0, 8, m) < eighths).astype(np.int32)
     t = _build(dim, lf)
+    assert _was_sliced(t, m) == sliced
     _check_table(t, dim)
     assert np.array_equal(_filter_words(t), _bloom_words(keys[dim["flag"] == 1], t.handle.filter_bits // 32))
 
 
 def test_without_the_extra_workspace():
-    keys = np.random.default_rng(1).choice(1 << 31, 600_000, replace=False).astype(np.int32)
+    keys = np.random.default_rng(1).choice(1 << 31, 800_000, replace=False).astype(np.int32)
     dim = _dims(keys, 1)
     _check_table(_build(dim, 0.5, workspace_extra=False), dim)
 
 
 def test_uneven_hashes_fall_back_to_inserts():
-    """All hashes in the lower half: the slices there overfill."""
+    """All hashes in the lower three eighths: half of the slices there overfill."""
     inv = pow(K, -1, 1 << 32)
-    h = np.random.default_rng(2).choice(1 << 31, 1 << 19, replace=False).astype(np.uint64)
+    h = np.random.default_rng(2).choice(3 << 29, 3 << 18, replace=False).astype(np.uint64)
     keys = ((h * np.uint64(inv)) & np.uint64(0xFFFFFFFF)).astype(np.uint32).view(np.int32)
     dim = _dims(keys, 2)
     t = _build(dim, 0.5)
+    assert not _was_sliced(t, keys.size)      # (given up before a row was moved)
     _check_table(t, dim)
     assert np.array_equal(_filter_words(t), _bloom_words(keys[dim["flag"] == 1], t.handle.filter_bits // 32))
 
@@ -98,11 +113,11 @@ def test_full_slices_between_overfull_ones():
     rng = np.random.default_rng(8)
     per = 1 << 12
     h = []
-    for q in range(0, 150, 2):
+    for q in range(0, 222, 2):
         h.append((q * per + per // 2) * 4096 + rng.choice(per // 2 * 4096, 3000, replace=False))
         h.append((q + 1) * per * 4096 + rng.choice(per * 4096, per + 50, replace=False))
     h = np.concatenate(h).astype(np.uint64)
-    assert h.size >= 1 << 19 and h.size / 0.9 <= 1 << 20
+    assert h.size >= 3 << 18 and h.size / 0.9 <= 1 << 20
     keys = ((h * np.uint64(pow(K, -1, 1 << 32))) & np.uint64(0xFFFFFFFF)).astype(np.uint32).view(np.int32)
     dim = _dims(rng.permutation(keys), 8)
     t = _build(dim, 0.9)
@@ -113,7 +128,7 @@ def test_full_slices_between_overfull_ones():
 
 def test_duplicates_are_reported():
     from paper_2607_07632_amd import sdb
-    keys = np.random.default_rng(3).permutation(600_000).astype(np.int32) * 7
+    keys = np.random.default_rng(3).permutation(800_000).astype(np.int32) * 7
     keys[-1] = keys[5]
     with pytest.raises(sdb.SdbError) as e:
         _build(_dims(keys, 3), 0.5)
@@ -122,8 +137,8 @@ def test_duplicates_are_reported():
 
 def test_two_sliced_tables_and_a_dense_one_in_one_batch():
     rng = np.random.default_rng(4)
-    a = rng.choice(1 << 31, 600_000, replace=False).astype(np.int32)
-    b = rng.choice(1 << 31, 530_000, replace=False).astype(np.int32)
+    a = rng.choice(1 << 31, 900_000, replace=False).astype(np.int32)
+    b = rng.choice(1 << 31, 790_000, replace=False).astype(np.int32)
     n = 200_003
     fact = {"ka": a[rng.integers(0, a.size, n)], "kb": b[rng.integers(0, b.size, n)],
             "kc": rng.integers(0, 1000, n, dtype=np.int32), "v": rng.integers(-10**6, 10**6, n, dtype=np.int32)}
