@@ -378,6 +378,7 @@ typedef struct sdb_plan {
     int32_t n_stages;
     int32_t stage_kind[SDB_MAX_STAGES];
     int32_t stage_index[SDB_MAX_STAGES];
+    int32_t item_rows;                    /* fact rows per item of the fused kernel: 4 or 1 (`vector` says when) */
     double stage_pass[SDB_MAX_STAGES];    /* pass fraction on the sample among the sampled rows that
                                              pass every earlier stage (conditional), or the estimate
                                              used (the dimension's pass fraction) without a sample */

@@ -105,7 +105,7 @@ class SdbQuery(C.Structure):
 
 class SdbPlan(C.Structure):
     _fields_ = [("n_stages", i32), ("stage_kind", i32 * MAX_STAGES),
-                ("stage_index", i32 * MAX_STAGES), ("stage_pass", C.c_double * MAX_STAGES),
+                ("stage_index", i32 * MAX_STAGES), ("item_rows", i32), ("stage_pass", C.c_double * MAX_STAGES),
                 ("stage_pass_alone", C.c_double * MAX_STAGES),
                 ("stage_lds", i32 * MAX_STAGES), ("stage_defer", i32 * MAX_STAGES),
                 ("stage_range", i32 * MAX_STAGES), ("stage_coarse", i32 * MAX_STAGES),
@@ -620,7 +620,7 @@ def plan_summary(plan: SdbPlan, query: dict | None = None) -> dict:
                     st["prefilter"] = True
         stages.append(st)
     return {"stages": stages, "terminal": TERMINAL_NAMES.get(plan.terminal, plan.terminal),
-            "ipt": plan.ipt, "vector": plan.vector, "eager": plan.eager, "block": plan.block, "grid": plan.grid,
+            "ipt": plan.ipt, "item_rows": plan.item_rows, "vector": plan.vector, "eager": plan.eager, "block": plan.block, "grid": plan.grid,
             "xcd_copies": plan.xcd_copies, "lds_bytes": plan.lds_bytes,
             "n_parts": plan.n_parts, "part_subs": plan.part_subs, "part_cap": int(plan.part_cap),
             "slice_bits": plan.slice_bits, "slice_lds": plan.slice_lds,

@@ -1,6 +1,7 @@
-"""4-row items on columns that are not 16-byte aligned: every terminal, row
-counts around an item and a tile, columns at different offsets, each against
-the oracle and against 1-row items."""
+"""4-row items on columns that are not 16-byte aligned: every terminal, one and
+two items per lane, row counts around an item and a tile, columns at different
+offsets, each against the oracle and against 1-row items (which plans with a hash
+probe keep)."""
 
 import numpy as np
 import pytest
@@ -26,7 +27,8 @@ def _mixed_offsets(w):
 
 @pytest.mark.parametrize("name,force", [("c1_scalar_scan", None), ("c2_join_group", None), ("c3_star3", None),
                                         ("c3_star3", {"terminal": "part"}), ("c3_star3", {"segments": 1}),
-                                        ("c4_star4_zipf", None), ("c5_hash_stress", None)])
+                                        ("c4_star4_zipf", None), ("c3_star3", {"ipt": 2}), ("c4_star4_zipf", {"ipt": 2}),
+                                        ("c5_hash_stress", None)])
 @pytest.mark.parametrize("n", [1, 3, 4, 2047, 2049, 300_007])
 def test_unaligned_columns(name, force, n):
     require_gpu()
@@ -34,8 +36,12 @@ def test_unaligned_columns(name, force, n):
     want = oracle_rows(w)
     dev = _mixed_offsets(w)
     got, q = run_gpu(w, force=force, dev=dev)
-    assert q.plan_obj.vector == 0 and q.plan_obj.unroll == 0
+    plan = q.plan_obj
+    assert plan.vector == 0 and plan.unroll == 0
+    assert plan.item_rows == (1 if name == "c5_hash_stress" else 4)
+    assert plan.ipt == (1 if name in ("c3_star3", "c4_star4_zipf") and not (force or {}).get("ipt") else 2)
     assert_same(got.as_rows(), want, f"{name} {n} rows {force}")
     if n == 300_007:
-        got, _ = run_gpu(w, force={**(force or {}), "vector": -1}, dev=dev)
+        got, q = run_gpu(w, force={**(force or {}), "vector": -1}, dev=dev)
+        assert q.plan_obj.item_rows == 1
         assert_same(got.as_rows(), want, f"{name} {n} rows {force}, 1-row items")

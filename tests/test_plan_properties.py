@@ -201,6 +201,8 @@ def check_plan(q, p):
     can_unroll = (p.vector == 1 and p.ipt == 2 and p.eager == 0 and p.block in (512, 1024) and n <= 4 and
                   not p.slice_bits and not hash_probe)
     assert p.unroll == (1 if can_unroll and q.force_unroll != -1 else 0)
+    # 4-row items on aligned columns, and on others but for hash probes; 1-row items can be forced
+    assert p.item_rows == (4 if p.vector or (q.force_vector != -1 and not hash_probe and not p.slice_bits) else 1)
 
 
 @settings(max_examples=400, deadline=None, suppress_health_check=[HealthCheck.too_slow])
@@ -264,6 +266,26 @@ def test_rank_and_deferred_placements_pass_run_validation(force_lds, force_block
     status = sdb.lib().sdb_run_star_query(C.byref(q), C.byref(p), 0x20000000, 0x30000000, int(p.n_groups),
                                           scratch, int(p.run_scratch_bytes), None)
     assert status in (OK, HIP_ERROR), (status, sdb.lib().sdb_last_error())
+
+
+@pytest.mark.parametrize("n,offset,terminal,ipt", [
+    (1 << 20, 4, 3, 1), ((1 << 20) + 1, 4, 3, 2), (1 << 20, 0, 3, 2), (1 << 20, 4, 2, 2), (1000, 4, 4, 1)])
+def test_items_per_lane_on_few_unaligned_rows(n, offset, terminal, ipt):
+    """One 4-row item per lane up to 2^20 rows of unaligned columns, into global terminals."""
+    d = sdb.SdbDim()
+    d.kind, d.width, d.n_rows, d.n_pass, d.n_slots = 1, 1, 1000, 500, 1000
+    d.key_min, d.key_max, d.sentinel, d.pass_key_min, d.pass_key_max = 0, 999, 0xFE, 0, 998
+    d.n_payloads, d.payload_radix[0], d.payload_div[0], d.domain = 1, 25, 1, 25
+    d.map, d.bits = 0x400000, 0x200000
+    q = sdb.SdbQuery()
+    q.n_fact, q.n_cols, q.n_joins, q.n_group_keys = n, 2, 1, 1
+    q.cols[0], q.cols[1] = 0x1000000 + offset, 0x2000000 + offset
+    q.joins[0], q.group_keys[0], q.agg = sdb.SdbJoin(0, C.pointer(d)), sdb.SdbGroupKey(0, 0), sdb.SdbAgg(0, 1, 0)
+    q.force_order, q.grid_blocks, q.force_terminal = 1, 64, terminal
+    p = sdb.SdbPlan()
+    assert sdb.lib().sdb_plan_star_query(C.byref(q), None, 0, None, C.byref(p)) == OK, sdb.lib().sdb_last_error()
+    check_plan(q, p)
+    assert p.item_rows == 4 and p.ipt == ipt
 
 
 def _c5_like(n_fact, hash_bits=25, n_preds=1, agg_kind=0, aligned=True, filt=None, pass_frac=0.5):
