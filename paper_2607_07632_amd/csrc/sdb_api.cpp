@@ -310,7 +310,8 @@ bool hash_slices(const sdb_dim_desc* desc, const BuildParams& bp, int64_t n_pass
     hp->part_count = (uint32_t*)take(P * 4);
     hp->part_start = (uint32_t*)take((P + 1) * 4);
     hp->chunk_start = (uint32_t*)take((P + 1) * 4);
-    hp->spill_n = (uint32_t*)take(4);
+    hp->spill_n = (uint32_t*)take(8);
+    hp->over = hp->spill_n + 1;
     hp->rec = (unsigned long long*)take(n * 8);
     hp->spill = (unsigned long long*)take((uint64_t)hp->spill_cap * 8);
     return off <= workspace_bytes;

@@ -310,6 +310,7 @@ struct HashSliceParams {
     uint32_t* part_start;
     uint32_t* chunk_start;
     uint32_t* spill_n;         // rows whose slots lie past their slice's end
+    uint32_t* over;            // 1: a slice has more rows than slots, none is built (spill_n's neighbour)
     unsigned long long* rec;   // slot values, slice after slice
     unsigned long long* spill; // spill_cap of them
 };
@@ -362,6 +363,9 @@ struct PartParams {
     uint32_t* item_cnt;
     unsigned long long* sums;
     unsigned long long* counts;
+    uint32_t* over;            // set to 1 where a partition holds more than max_part records (null: not asked)
+    uint32_t max_part;
+    uint32_t pad_;
 };
 
 struct v4u_t {

@@ -1161,7 +1161,10 @@ __global__ void __launch_bounds__(256) part_offsets_kernel(PartParams pp) {
         const uint32_t n = min(4096u, pp.n_regions - b0);
         carry += block_scan_256(h + b0, h + b0, n, carry, wtmp);
     }
-    if (threadIdx.x == 0) pp.part_count[blockIdx.x] = carry;
+    if (threadIdx.x == 0) {
+        pp.part_count[blockIdx.x] = carry;
+        if (pp.over && carry > pp.max_part) *pp.over = 1u;
+    }
 }
 
 // One block per fused-kernel region: the region's records, kScatterChunk at a
@@ -2321,7 +2324,10 @@ __global__ void __launch_bounds__(kSliceBlock) hash_count_kernel(HashSliceParams
     __shared__ uint32_t lh[1 << kSliceMaxBits];
     const uint32_t P = 1u << hp.bits;
     for (uint32_t q = threadIdx.x; q < P; q += kSliceBlock) lh[q] = 0u;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *hp.spill_n = 0u;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *hp.spill_n = 0u;
+        *hp.over = 0u;
+    }
     __syncthreads();
     const int64_t r0 = (int64_t)blockIdx.x * hp.rows_per_block;
     const int64_t r1 = min(hp.bp.n, r0 + hp.rows_per_block);
@@ -2341,11 +2347,8 @@ __global__ void __launch_bounds__(kSliceBlock) hash_count_kernel(HashSliceParams
 __global__ void __launch_bounds__(kSliceBlock) hash_scatter_kernel(HashSliceParams hp) {
     // a slice with more rows than slots cannot be built: no pass does anything
     // from here on, and the host builds the table with inserts
-    bool over = false;
-    for (uint32_t q = threadIdx.x; q < 1u << hp.bits; q += kSliceBlock)
-        over = over || hp.part_count[q] > (uint32_t)(hp.bp.nslots >> hp.bits);
-    if (__syncthreads_or(over)) {
-        if (threadIdx.x == 0) atomicOr(&hp.bp.stats->dup, kHashSliceRetry);
+    if (*hp.over) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&hp.bp.stats->dup, kHashSliceRetry);
         return;
     }
     SliceParams sp;
@@ -2397,10 +2400,7 @@ __global__ void __launch_bounds__(1024) hash_slice_kernel(HashSliceParams hp) {
     const BuildParams& bp = hp.bp;
     const uint32_t q = blockIdx.x, per = (uint32_t)(bp.nslots >> hp.bits);
     const uint32_t r0 = hp.part_start[q], n = hp.part_start[q + 1] - r0;
-    // (read by one thread: a block that spills past the capacity sets the flag meanwhile)
-    if (__syncthreads_or(threadIdx.x == 0 && (__hip_atomic_load(&bp.stats->dup, __ATOMIC_RELAXED,
-                                                                __HIP_MEMORY_SCOPE_AGENT) & kHashSliceRetry)))
-        return;
+    if (*hp.over) return;
     for (uint32_t i = threadIdx.x; i < per; i += 1024u) slots[i] = 0ull;
     __syncthreads();
     constexpr int U = 8;
@@ -2466,6 +2466,8 @@ hipError_t launch_hash_slices(const HashSliceParams& hp, hipStream_t s) {
     pp.part_start = hp.part_start;
     pp.chunk_start = hp.chunk_start;
     pp.chunk_rows = (uint32_t)kPartChunk;
+    pp.over = hp.over;
+    pp.max_part = (uint32_t)(hp.bp.nslots >> hp.bits);
     hipLaunchKernelGGL(part_offsets_kernel, dim3(P), dim3(256), 0, s, pp);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(part_scan_kernel, dim3(1), dim3(1024), 0, s, pp);
