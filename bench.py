@@ -66,15 +66,18 @@ PAPER_CONTEXT = {
 ONE_CORE_ROWS = 8_000_000        # rows of the one-core oracle timings (c1 whole, c2 and c3 a head)
 # the fused kernel's source: its template and the device helpers it uses
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2607_07632_amd", "csrc", f) for f in ("sdb_fused.h", "sdb_device.h")]
+SLICE_SOURCES = [os.path.join(ROOT, "paper_2607_07632_amd", "csrc", "sdb_kernels.hip")]
 
 
 def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def kernel_source_hash() -> str:
+def kernel_source_hash(workload: str) -> str:
+    """Of the sources of the kernels in the workload's timed window (c5's are the
+    sliced probe's)."""
     h = hashlib.sha256()
-    for path in KERNEL_SOURCES:
+    for path in KERNEL_SOURCES + (SLICE_SOURCES if workload == "c5_hash_stress" else []):
         h.update(open(path, "rb").read())
     return h.hexdigest()[:16]
 
@@ -88,7 +91,7 @@ def traffic_from_profile(workload: str):
     text = open(path).read()
     m_hash = re.search(r"kernel_source_sha256_16:\s*([0-9a-f]+)", text)
     m_bytes = re.search(r"hbm_bytes_per_launch:\s*([0-9.eE+]+)", text)
-    if not m_hash or not m_bytes or m_hash.group(1) != kernel_source_hash():
+    if not m_hash or not m_bytes or m_hash.group(1) != kernel_source_hash(workload):
         return None
     return float(m_bytes.group(1))
 
@@ -168,8 +171,9 @@ ABLATION_RUNGS = [
     ("planner's choice (terminal, block size, rank tables)", {"slice": -1, "unroll": -1, "window": -1}),
     ("+ stage loop written out (plans without a hash probe)", {"slice": -1, "window": -1}),
     ("+ LDS window over the busiest device-memory map", {"slice": -1}),
-    ("+ a hash probe over 2 MiB table slices", {"prefilter": -1}),
-    ("+ rows the table's pass filter rejects dropped before the slicing (planner's choice)", {}),
+    ("+ a hash probe over 2 MiB table slices", {"prefilter": -1, "slices_in": "l2"}),
+    ("+ rows the table's pass filter rejects dropped before the slicing", {"prefilter": 1}),
+    ("+ more slices, summed by dimension row in LDS, no filter read (planner's choice)", {}),
 ]
 
 
@@ -183,6 +187,7 @@ def ablation_ladder(sdb, fact, dims, wdims, query, stream, base_force) -> list:
         force = dict(base_force)
         force.update(f)
         baseline = force.pop("baseline", None)
+        slices_in = force.pop("slices_in", None)
         rq = query
         if force.pop("tables", None) == "hash":
             rq = copy.deepcopy(query)
@@ -194,6 +199,8 @@ def ablation_ladder(sdb, fact, dims, wdims, query, stream, base_force) -> list:
         try:
             q = sdb.StarQuery(fact, tabs, rq, force)
             plan = q.plan()
+            if slices_in == "l2":
+                plan.slice_lds = 0
         except sdb.SdbError as e:
             out.append({"rung": name, "force": f, "run_ms": float("nan"), "error": str(e), "plan": None})
             continue

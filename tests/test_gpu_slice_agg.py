@@ -160,6 +160,40 @@ def test_the_planners_route_and_a_scratch_that_holds_the_other_alone():
         assert_same(got.as_rows(), want, f"{force} {lds} {short}")
 
 
+def test_the_route_in_a_graph():
+    """Captured with the compaction and replayed three times, outputs and scratch
+    scribbled over and other work done in between."""
+    import torch
+    from paper_2607_07632_amd import sdb
+    require_gpu()
+    keys = np.random.default_rng(17).choice(1 << 31, 30_000, replace=False).astype(np.int32)
+    w = _workload(keys, 150_001, 17, groups=5000)
+    want = oracle_rows(w)
+    fact, dims = upload(w)
+    q = sdb.StarQuery(fact, sdb.build_dims(dims, w.dim_keys, w.query), w.query, {"slice": 1})
+    plan = q.plan()
+    plan.slice_lds = 8
+    scratch = torch.empty(int(plan.run_scratch_bytes) + (64 << 20), dtype=torch.uint8, device="cuda")
+    sums, counts = q.alloc_outputs()
+    q.run(sums, counts, scratch=scratch)
+    out = q.finalize(sums, counts)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        q.run(sums, counts, scratch=scratch)
+        q.finalize(sums, counts, outputs=out)
+    for i in range(3):
+        for t in (sums, counts, scratch, *out):
+            t.fill_(0x5A + i)
+        (fact["value"].sum() + i).item()
+        graph.replay()
+        torch.cuda.synchronize()
+        k, s, c, n, _ = out
+        m = int(n.item())
+        got = sdb.QueryResult(k[:m].to(torch.int64).cpu().numpy(), s[:m].cpu().numpy(), c[:m].cpu().numpy())
+        assert_same(got.as_rows(), want, f"replay {i}")
+
+
 @pytest.mark.parametrize("agg,lds", [("col", 9), ("sub", 9)])
 def test_a_large_table_few_of_whose_rows_pass(agg, lds):
     """2^23 dimension rows in 2^24 slots, a tenth passing: 512 slices of 2^15
