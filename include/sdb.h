@@ -369,9 +369,9 @@ enum { SDB_LDS_GLOBAL = 0, SDB_LDS_MAP = 1, SDB_LDS_BITS = 2, SDB_LDS_RANK = 3, 
  * there, so it tests no pass filter and launches no fused kernel. The planner
  * takes it from 2^24 fact rows on where the passing rows of a 2,048th of the
  * table fit an LDS table (up to about 8.9M passing rows, at most 2^26 slots),
- * unless the pre-filter is forced or keeps so few rows that the route above is
- * the faster one (2% at 1,024 slices or more; with two-column aggregates 4% to
- * 13%). run_scratch_bytes counts its rows; a run whose scratch
+ * unless the pre-filter is forced, or the pre-filter keeps (2% at 1,024 slices or
+ * more; with two-column aggregates 4% to 13%) or the predicates leave so few
+ * rows that the route above is the faster one. run_scratch_bytes counts its rows; a run whose scratch
  * does not hold them takes the route above, which the other fields describe,
  * if it holds that one's. */
 typedef struct sdb_plan {

@@ -1176,7 +1176,15 @@ int slice_agg_bits(const sdb_dim* d) {
 // 2,124). Records of two values cost it more: 256 slices break even at 10% of
 // 200M rows (2,143 against 2,190) and 3% of 40M (440 against 443), 1,024 at
 // about 13% (200M: 2,690 against 2,600 to 2,748; 40M: 629 against 623 to 664).
-bool slice_lds_pays(const sdb_query* q, int bits, double kept) {
+// And it reads the whole table and fills its LDS tables from it, however few of
+// the n fact rows the predicates leave (`rows`): 16.8M dimension rows, half
+// passing, one value, 17M fact rows, 0.17M left 285 against 216 us, 0.85M 302
+// against 269, 3.4M 326 against 335, 8.5M 358 against 429; 40M rows, 0.4M left
+// 384 against 342, 2M 402 against 468; 200M, 2M 1,205 against 1,339. A quarter
+// of the dimension rows: 17M rows, 0.17M left 157 against 182.
+bool slice_lds_pays(const sdb_query* q, const sdb_dim* d, int bits, double kept, double rows) {
+    const double left = (q->agg.kind == SDB_AGG_COL ? 12.0 : 6.0) * rows;
+    if (left + 0.5 * (double)q->n_fact < (double)d->n_slots) return false;
     if (q->agg.kind == SDB_AGG_COL) return bits < 10 || kept > 0.02;
     return kept > (bits >= 10 ? 0.13 : q->n_fact >= (1ll << 26) ? 0.10 : 0.04);
 }
@@ -2116,7 +2124,12 @@ SDB_API sdb_status sdb_plan_star_query(const sdb_query* q, void* scratch, int64_
         // the LDS route, from the row count on that the planner takes slices by
         // itself (a smaller, forced plan runs through L2), with its rows and records
         const int lds_bits = slice_agg_bits(d);
-        if (q->n_fact >= kSliceMinRows && q->force_prefilter != 1 && slice_lds_pays(q, lds_bits, kept))
+        double rows = (double)q->n_fact;   // past the fact predicates
+        uint32_t preds = 0;
+        for (int s = 0; s < n; ++s)
+            if (plan->stage_kind[s] == 0) preds |= 1u << bit[s];
+        if (preds && smp.have) rows *= smp.frac(preds);
+        if (q->n_fact >= kSliceMinRows && q->force_prefilter != 1 && slice_lds_pays(q, d, lds_bits, kept, rows))
             plan->slice_lds = lds_bits;
         if (plan->slice_lds > 0)
             plan->run_scratch_bytes = std::max(plan->run_scratch_bytes, (int64_t)slice_agg_layout(q, plan).total +

@@ -220,3 +220,8 @@ def test_a_large_table_few_of_whose_rows_pass(agg, lds):
         plan.slice_lds = lds
         q.run(*again)
         assert bool((sums == again[0]).all()) and bool((counts == again[1]).all())
+        # so few rows past the predicate do not pay for reading the whole table: through L2
+        w.query["fact_preds"][0]["lo"] = 2_080_000_000
+        few = sdb.StarQuery(fact, q.tables, w.query)
+        assert few.plan().slice_lds == 0 and few.plan_obj.slice_bits > 0
+        assert_same(few.execute().as_rows(), oracle_rows(w), "few rows")
