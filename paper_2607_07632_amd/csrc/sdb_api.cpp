@@ -2291,6 +2291,9 @@ SDB_API sdb_status sdb_run_star_query(const sdb_query* q, const sdb_plan* plan, 
         sp.out_rec = (unsigned long long*)(slice_base + AL.rec);
         sp.out_val2 = sp.val2_col >= 0 ? (int32_t*)(slice_base + AL.rec_b) : nullptr;
         sp.item_rows = kSliceAggItem;
+        const uint64_t even = (uint64_t)q->n_fact >> plan->slice_lds;
+        sp.skew_rows = (uint32_t)std::min<uint64_t>(kSliceAggSkewMax, std::max<uint64_t>(kSliceAggSkewMin, even));
+        sp.skew_over = (uint32_t)std::min<uint64_t>(even + even / 2, 0xFFFFFFFFull);
         ap.st = p.st[plan->slice_stage];
         ap.bits = plan->slice_lds;
         ap.agg_kind = q->agg.kind;

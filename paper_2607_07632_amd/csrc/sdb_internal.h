@@ -97,6 +97,10 @@ constexpr int kSliceAggSlotBits = 15;
 constexpr int kSliceAggHashBits = 15;      // a 16-bit entry number per hash value: 64 KB ...
 constexpr uint32_t kSliceAggEntries = 4608;     // ... of entries of 18 bytes (key, table slot, rows, sum): 81 KB
 constexpr uint32_t kSliceAggItem = 1u << 19;
+// A partition half as large again as an even share of all rows has hot keys,
+// whose rows add to one LDS address: items of an even share, within these
+// bounds, so that more blocks add them (see launch of the LDS route).
+constexpr uint32_t kSliceAggSkewMin = 1u << 15, kSliceAggSkewMax = 1u << 18;
 constexpr uint32_t kSliceAggMaxGroups = 1024;   // groups summed per block in LDS beside the table (12 bytes each)
 // more groups: the entries leave as records by range of 2^kSliceEmitShift
 // groups, which slice_merge_kernel sums in LDS kSliceEmitChunk at a time
@@ -353,6 +357,8 @@ struct PartParams {
     const void* rec_val;
     int32_t rec_wide;
     uint32_t chunk_rows;       // records per aggregation work item
+    uint32_t skew_rows;        // > 0: ... of a partition with more than skew_over of them
+    uint32_t skew_over;
     uint32_t* part_hist;       // [q * n_regions + b]: counts, then exclusive offsets within partition q
     uint32_t* part_count;      // records per partition
     uint32_t* part_start;      // n_parts + 1 entries
@@ -365,7 +371,6 @@ struct PartParams {
     unsigned long long* counts;
     uint32_t* over;            // set to 1 where a partition holds more than max_part records (null: not asked)
     uint32_t max_part;
-    uint32_t pad_;
 };
 
 struct v4u_t {
@@ -416,6 +421,8 @@ struct SliceParams {
     int32_t* out_val2;         // val2_col >= 0: the second operands
     unsigned long long* out_rec;   // LDS route: {key, value} pairs in place of out_key and out_val
     uint32_t item_rows;        // LDS route: rows per work item (chunk_start)
+    uint32_t skew_rows;        // ... of a partition with more than skew_over rows
+    uint32_t skew_over;
     uint32_t pad_;
     // tile order of the fused launch over them: its tiles of tile_rows rows;
     // XCD x (x = q mod 8) walks the tiles whose first row lies in partition q

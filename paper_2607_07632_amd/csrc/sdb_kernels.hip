@@ -1087,7 +1087,8 @@ __global__ void __launch_bounds__(1024) part_scan_kernel(PartParams pp) {
     for (uint32_t base = 0; base < pp.n_parts; base += 1024u) {
         const uint32_t i = base + threadIdx.x;
         const uint32_t vr = i < pp.n_parts ? pp.part_count[i] : 0u;
-        const uint32_t vc = vr / pp.chunk_rows + (vr % pp.chunk_rows != 0u ? 1u : 0u);
+        const uint32_t per = pp.skew_rows && vr > pp.skew_over ? pp.skew_rows : pp.chunk_rows;
+        const uint32_t vc = vr / per + (vr % per != 0u ? 1u : 0u);
         buf_r[threadIdx.x] = vr;
         buf_c[threadIdx.x] = vc;
         __syncthreads();
@@ -1884,6 +1885,8 @@ hipError_t launch_slice_partition(const SliceParams& sp, int grid, hipStream_t s
     pp.part_start = sp.part_start;
     pp.chunk_start = sp.chunk_start;
     pp.chunk_rows = sp.out_rec ? sp.item_rows : (uint32_t)kPartChunk;
+    pp.skew_rows = sp.out_rec ? sp.skew_rows : 0u;
+    pp.skew_over = sp.skew_over;
     hipLaunchKernelGGL(part_offsets_kernel, dim3(P), dim3(256), 0, s, pp);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -2023,6 +2026,28 @@ __device__ __forceinline__ void slice_fill_table(const SliceAggParams& ap, uint3
 // issued before this one's lookups; the first lookups of its rows are made
 // together, and the rows that met another key go on one by one.
 constexpr int kAggPairs = 3;
+// Atomics of one address are performed one after the other, so where a wave
+// holds at least kAggSame rows of its first row's key it adds them up itself.
+constexpr int kAggSame = 32;
+
+// The sum over the wave, in lane 63: shifts within the rows of 16 lanes, then
+// the rows' last lanes to the rows after them. (Through LDS, as __shfl_xor
+// does, the sums would cost what the atomics do.)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned long long dpp_add_u64(unsigned long long v) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROWS, 0xF, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, ROWS, 0xF, true);
+    return v + (((unsigned long long)hi << 32) | lo);
+}
+__device__ __forceinline__ unsigned long long wave_last_sum_u64(unsigned long long v) {
+    v = dpp_add_u64<0x111, 0xF>(v);   // row_shr:1
+    v = dpp_add_u64<0x112, 0xF>(v);
+    v = dpp_add_u64<0x114, 0xF>(v);
+    v = dpp_add_u64<0x118, 0xF>(v);
+    v = dpp_add_u64<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
+    v = dpp_add_u64<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
+    return v;
+}
 
 template <bool TWO>
 __device__ __forceinline__ void slice_load_pairs(const unsigned long long* rec, const int32_t* rec_b, uint32_t at,
@@ -2078,9 +2103,24 @@ __device__ __forceinline__ void slice_add_rows(const SliceAggParams& ap, uint32_
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) k[u] = t.key[e[u] != kAggFree ? e[u] : 0u];
+        // many rows of one key (looked for in the first of the step's rows only)
+        const uint32_t lead_key = (uint32_t)__builtin_amdgcn_readfirstlane((int)key[0]);
+        const bool many = __popcll(__ballot(key[0] == lead_key)) >= kAggSame;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (e[u] != kAggFree && k[u] != key[u]) e[u] = slice_find(t, key[u], (h[u] + 1u) & (kAggHashes - 1u));
+            if (many) {
+                const uint32_t lead = (uint32_t)__builtin_amdgcn_readfirstlane((int)e[u]);
+                const unsigned long long same = __ballot(e[u] == lead);
+                if (lead != kAggFree && __popcll(same) >= kAggSame) {
+                    const unsigned long long sum = wave_last_sum_u64(e[u] == lead ? (unsigned long long)v[u] : 0ull);
+                    if ((threadIdx.x & 63u) == 63u) {
+                        atomicAdd(&t.rows[lead], (uint32_t)__popcll(same));
+                        atomicAdd(&t.sum[lead], sum);
+                    }
+                    if (e[u] == lead) e[u] = kAggFree;
+                }
+            }
             if (e[u] != kAggFree) {
                 atomicAdd(&t.rows[e[u]], 1u);
                 atomicAdd(&t.sum[e[u]], (unsigned long long)v[u]);

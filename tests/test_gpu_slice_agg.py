@@ -108,8 +108,26 @@ def test_records_past_a_ranges_capacity():
     _check(w)
 
 
+@pytest.mark.parametrize("share", [0.3, 0.6, 1.0])
+@pytest.mark.parametrize("groups,agg", [(700, "col"), (5000, "mul"), (5000, "col")])
+def test_hot_keys_among_others(share, groups, agg):
+    """Rows that a wave adds up itself beside others of its slice, misses and
+    rows that do not pass, over many work items of two slices; two hot keys,
+    the int32 extremes among their values."""
+    rng = np.random.default_rng(18)
+    keys = rng.choice(1 << 31, 40_000, replace=False).astype(np.int32)
+    n = 300_007
+    w = _workload(keys, n, 18, groups=groups, agg=agg)
+    w.dims["big"]["flag"][:3] = 1, 1, 0
+    hot = keys[np.minimum(rng.integers(0, 6, n), 2)[:n]]        # the third is filtered out
+    w.fact["key"][:] = np.where(rng.random(n) < share, hot, w.fact["key"])
+    w.fact["value"][:64] = -(1 << 31)
+    w.fact["other"][64:128] = (1 << 31) - 1
+    _check(w)
+
+
 def test_a_hot_key_over_several_work_items():
-    """1.2M rows of one key (three work items of one partition), the int32
+    """1.2M rows of one key (many work items of one partition), the int32
     extremes among their values."""
     keys = np.arange(-500, 500, dtype=np.int32)
     n = 1_200_003
