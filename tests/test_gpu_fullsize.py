@@ -8,7 +8,7 @@ launch configuration the benchmark times, against the oracle itself.
   workers also return the 64-bit sum of every fact column of their rows, which
   must equal the sums of the device columns the GPU read.
 * The oracle on a window of the same device columns starting at an unaligned
-  row (the kernel's 1-row item path).
+  row (unaligned columns).
 * Row-range additivity on the GPU: three unaligned slices of the full columns
   add up to the full result.
 """
@@ -107,7 +107,7 @@ def test_more_than_2g_rows(oracle_pool):
     """c3's query over 2^31 + 4,099 fact rows from the same seeded generator:
     64-bit row indexing end to end. Every group against the oracle over all
     rows (row ranges on the worker pool, merged), and two row ranges, the
-    second starting at an unaligned row (1-row items), add up to the whole."""
+    second starting at an unaligned row, add up to the whole."""
     import torch
     from paper_2607_07632_amd import sdb
     n = 2**31 + 4099
