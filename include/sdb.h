@@ -272,8 +272,10 @@ typedef struct sdb_agg {
  *                  the blocks per CU, for the dense device-memory stage it
  *                  serves most; k >= 2: the same with at most 128 * k slots
  *  force_prefilter the sliced hash probe's pre-filter (sdb_plan.slice_prefilter):
- *                  0: the planner's choice; -1: never; 1: whenever the plan
- *                  slices a hash probe into a table with a pass filter */
+ *                  0: the planner's choice; -1: never, nor the filter before
+ *                  an unsliced probe; 1: whenever the plan slices a hash probe
+ *                  into a table with a pass filter, and then through L2
+ *                  (slice_lds 0) */
 typedef struct sdb_query {
     int64_t n_fact;
     int32_t n_cols;
