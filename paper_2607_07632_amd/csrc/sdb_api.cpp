@@ -465,6 +465,8 @@ bool probe_filter(const sdb_query* q, const sdb_plan* plan, int s) {
     return p + (1.0 - p) * fp <= line;
 }
 
+constexpr int64_t kTogetherFewRows = 1 << 20, kTogetherManyRows = 8'000'000;
+
 // Whether a plan with a hash probe runs the instances whose rows go through
 // their chains together, two slots a turn (stage_probe), and not row by row,
 // one slot at a time (stage_hash). Together pays where a turn's latency is
@@ -476,7 +478,11 @@ bool probe_filter(const sdb_query* q, const sdb_plan* plan, int s) {
 // 183.9 -> 178.7; 16 MiB 0.32 191.4 -> 187.4, 0.5 210.7 -> 201.9, 0.88 901 ->
 // 961; 64 MiB 0.5 265.2 -> 249.5. Over table slices of 2 MiB, 150M rows: 2^25
 // slots 0.3 full 3,256 -> 3,098, 0.5 3,820 -> 3,317, 0.88 13,407 -> 10,383;
-// 2^26 slots 0.26 3,450 -> 3,535, 0.34 3,602 -> 3,573.
+// 2^26 slots 0.26 3,450 -> 3,535, 0.34 3,602 -> 3,573. Few rows, a tile or less
+// per compute unit, are bound by latency: 100K rows, 8 MiB 0.5 full 18.8 -> 15.4,
+// 1M 29.3 -> 25.1; with a few tiles a unit row by row is no slower or faster: 2M
+// rows 4 MiB 0.5 full 38.8 -> 44.0, two joins, 16 MiB 62.3 -> 65.0, 4M rows 0.3 full
+// 69.8 -> 72.2, two joins, 4 MiB 0.75 full 152.5 -> 164.2.
 bool probes_together(const sdb_query* q, const sdb_plan* plan) {
     const sdb_dim* d = largest_probed(q, plan);
     const double load = (double)d->n_rows / (double)d->n_slots;
@@ -484,6 +490,8 @@ bool probes_together(const sdb_query* q, const sdb_plan* plan) {
     for (int s = 0; s < plan->n_stages; ++s)
         if (probe_filter(q, plan, s)) return true;
     if (load > 0.8) return false;
+    if (q->n_fact <= kTogetherFewRows) return true;
+    if (q->n_fact < kTogetherManyRows) return false;
     const uint64_t bytes = d->n_slots * 8u;
     return bytes >= (16ull << 20) || load >= (bytes <= (2ull << 20) ? 0.42 : 0.55);
 }
